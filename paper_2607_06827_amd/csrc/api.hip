@@ -706,8 +706,7 @@ static int prefill_attn_bwd_impl(const void* q, int32_t batch, int32_t num_q_hea
   const int rows_per_tile = skv::prefill_bwd_rows_per_tile(cache->dtype, group);
   const int64_t q_tiles = (spans->max_total_len + rows_per_tile - 1) / rows_per_tile;
   const int64_t keys = spans->max_total_len < hat_capacity ? spans->max_total_len : hat_capacity;
-  const int keys_per_block = skv::prefill_bwd_keys_per_block(cache->dtype, cache->head_dim);
-  const int64_t key_tiles = (keys + keys_per_block - 1) / keys_per_block;
+  const int64_t key_tiles = (keys + skv::kMinKeysPerBlock - 1) / skv::kMinKeysPerBlock;
   if ((int64_t)batch * cache->num_kv_heads * q_tiles > INT32_MAX ||
       (int64_t)batch * cache->num_kv_heads * key_tiles > INT32_MAX)
     return SPEECHKV_ERR_INVALID_ARG;
@@ -728,7 +727,9 @@ static int prefill_attn_bwd_impl(const void* q, int32_t batch, int32_t num_q_hea
   a.q_len = q_len;
   a.num_q_heads = num_q_heads;
   a.num_q_tiles = (int)q_tiles;
-  a.num_key_tiles = (int)key_tiles;
+  a.q_rows = spans->max_total_len;
+  a.max_keys = (int)keys;
+  a.num_key_tiles = 0;
   a.scale = scale;
   a.scale_log2 = scale * 1.4426950408889634f;
   a.delta = static_cast<float*>(workspace);

@@ -29,7 +29,9 @@ struct PrefillBwdArgs {
   int q_len;
   int num_q_heads;
   int num_q_tiles;    // query tiles per (sequence, KV head), dQ kernel
-  int num_key_tiles;  // key blocks per (sequence, KV head), dK/dV kernel
+  int q_rows;         // bound on the rows of a sequence
+  int max_keys;       // bound on the keys of a sequence, min(compressed length bound, hat_cap)
+  int num_key_tiles;  // key blocks per (sequence, KV head), set by the dK/dV launch
   float scale;
   float scale_log2;
   float* delta;       // [B][Hq][q_len]: rowsum(dO * O), written by the dQ kernel
@@ -66,7 +68,7 @@ struct PoolBwdArgs {
 };
 
 int prefill_bwd_rows_per_tile(int dtype, int group);
-int prefill_bwd_keys_per_block(int dtype, int head_dim);  // keys of one dK/dV block
+constexpr int kMinKeysPerBlock = 16;  // fewest keys of a dK/dV block
 hipError_t launch_prefill_bwd(const PrefillBwdArgs& a, int dtype, int head_dim, int group,
                               int batch, hipStream_t s);
 // Slots of one sequence a pooling-backward block covers (a multiple of the

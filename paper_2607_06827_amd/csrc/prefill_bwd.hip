@@ -23,20 +23,19 @@
 //   stored output; the exact Delta accumulates beside it, and at the end
 //   dQ = scale (dZ0 K^ + (Delta0 - Delta) Kbar), Kbar = P K^.  It saves
 //   Delta for:
-// dK/dV kernel - a block owns 32 keys per wave (128 keys) of one (sequence,
-//   KV head) and walks the (query head, 32-row query tile) pairs that see
-//   them; each pair's Q / dO tile is staged once in LDS for all the waves
-//   (direct loads, three steps ahead), and each wave computes on its own keys,
-//   K and V held in registers
+// dK/dV kernel - a block owns a few keys (16 in fp32, 64 in bf16) of one
+//   (sequence, KV head) and walks the (query head, query tile) steps that see
+//   them; each step's Q / dO tile is staged in LDS by direct loads, K and V
+//   held in registers
 //     S = Q K^T,  dP = dO V^T               (queries x keys, one key per lane)
 //     dV^T += dO^T P,  dK^T += Q^T dZ        (dO^T, Q^T read transposed)
 //   starting S and dP from -LSE/scale and -Delta of their rows.
-// The fp32 kernels below run every product on the 32x32x2 fp32 MFMA.  The
-// bf16 kernels (further down) keep this split and these formulas on the
-// 16x16x32 bf16 MFMA with smaller per-wave tiles (16 query rows, or 16 keys, a
-// wave), so that three waves share each SIMD; P and dZ are rounded to bf16 as
-// MFMA operands, every product accumulates in fp32, and dK^ and dV^ are
-// written in fp32.
+// The fp32 kernels run every product on the fp32 MFMA (32x32x2 in dQ, 16x16x4
+// in dK/dV).  The bf16 kernels (further down) keep this split and these
+// formulas on the 16x16x32 bf16 MFMA with small per-wave tiles (16 query rows,
+// or 16 keys, a wave), so that three waves share each SIMD; P and dZ are
+// rounded to bf16 as MFMA operands, every product accumulates in fp32, and
+// dK^ and dV^ are written in fp32.
 // The mask's visibility rule comes from the span view (spans.hpp): one run
 // per sequence, or the runs of a segment table (kRuns).
 #include <climits>
@@ -51,12 +50,6 @@ namespace skv {
 namespace {
 
 constexpr float kLog2eF = 1.4426950408889634f;
-
-// s_waitcnt immediate that waits until at most n vector-memory operations of
-// the wave are outstanding (vmcnt in bits 3:0 and 15:14; expcnt and lgkmcnt
-// at their maxima, so they are not waited for)
-constexpr int wait_vmcnt(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
-static_assert(wait_vmcnt(0) == kWaitVmcnt0, "vmcnt(0) encoding");
 
 __device__ __forceinline__ float frag_dot(bf16x8_t x, bf16x8_t y) {
   float s = 0.f;
@@ -291,41 +284,6 @@ struct QTile {
   }
 };
 
-// A operand (kPack elements from element e) of row r of a swizzled tile
-__device__ __forceinline__ bf16x8_t tile_a(const bf16_bits* t, int off) {
-  return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(t + off));
-}
-__device__ __forceinline__ float tile_a(const float* t, int off) { return t[off]; }
-
-// Transposed A operand of a swizzled 32-row tile: what Mfma<T>::load_v
-// returns for a padded row-major tile (rows 16kk + 4(g/2) + j/4 (+8) for
-// bf16, row 8(kk/4) + 4hg + kk%4 for fp32; columns of head-dim block db).
-template <int D>
-__device__ __forceinline__ bf16x8_t tile_t(const bf16_bits* t, int kk, int db, int lane) {
-  typedef QTile<bf16_bits, D> Q;
-  const int g = lane >> 4, j = lane & 15;
-  const int r = 16 * kk + 4 * (g >> 1) + (j >> 2);
-  const int e = 32 * db + 16 * (g & 1) + 4 * (j & 3);
-  const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(t + Q::at(r, e)));
-  const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(t + Q::at(r + 8, e)));
-  const u16x8_t v = {(unsigned short)lo[0], (unsigned short)lo[1], (unsigned short)lo[2], (unsigned short)lo[3],
-                     (unsigned short)hi[0], (unsigned short)hi[1], (unsigned short)hi[2], (unsigned short)hi[3]};
-  return __builtin_bit_cast(bf16x8_t, v);
-}
-template <int D>
-__device__ __forceinline__ float tile_t(const float* t, int kk, int db, int lane) {
-  typedef QTile<float, D> Q;
-  return t[Q::at(8 * (kk / 4) + 4 * (lane >> 5) + (kk % 4), 32 * db + (lane & 31))];
-}
-
-template <typename T, int D>
-struct KvBwdShape {
-  // fp32 at d = 128 has twice the bytes per tile: two waves keep LDS in bounds
-  static constexpr int kWaves = (sizeof(T) == 4 && D == 128) ? 2 : 4;
-  static constexpr int kThreads = 64 * kWaves;
-  static constexpr int kKeys = 32 * kWaves;  // keys per block, 32 per wave
-};
-
 // Item of block bid in a dK/dV grid of nblk blocks over pairs x T key blocks
 // (items pair-major, pair = (sequence, KV head)).  The work of key block kt
 // falls with kt (later keys are seen by fewer query rows).  XCD x (= bid mod
@@ -337,6 +295,7 @@ struct KvBwdShape {
 // less time than ascending order everywhere).  The order is reversed within
 // whole pairs, so every item is still run exactly once.
 constexpr int kCusPerXcd = 32;
+constexpr int kCus = 8 * kCusPerXcd;
 __device__ __forceinline__ void dkdv_item(int bid, int nblk, int T, int& pair, int& kt) {
   const int xcd = bid & 7, per = nblk >> 3, rem = nblk & 7;
   const int item = xcd * per + min(xcd, rem) + (bid >> 3);
@@ -349,215 +308,240 @@ __device__ __forceinline__ void dkdv_item(int bid, int nblk, int T, int& pair, i
   kt = ((local / kCusPerXcd) & 1) ? T - 1 - kt0 : kt0;
 }
 
-template <typename T, int D, int G, bool kRuns>
-__global__ __launch_bounds__((KvBwdShape<T, D>::kThreads)) void prefill_bwd_dkdv_kernel(PrefillBwdArgs a) {
-  typedef Mfma<T> M;
-  typedef typename M::Frag Frag;
-  typedef QTile<T, D> Q;
-  constexpr int kWaves = KvBwdShape<T, D>::kWaves;
-  constexpr int kBlockKeys = KvBwdShape<T, D>::kKeys;
-  constexpr int kQ = 32;      // query rows per step
-  constexpr int kPack = M::kPack;
-  constexpr int kStep = 2 * kPack;
-  constexpr int kQChunks = D / kStep;
-  constexpr int kElems16 = Q::kElems16;
+// Heaviest-first order: block bid takes key block bid / pairs of pair bid %
+// pairs, so the first key blocks (which most query rows see) of every pair
+// start first and the lightest last, and when the pairs split evenly over the
+// eight XCDs every key block of a pair runs on the same one.
+__device__ __forceinline__ void dkdv_item_heaviest_first(int bid, int pairs, int& pair, int& kt) {
+  kt = bid / pairs;
+  pair = bid - kt * pairs;
+}
 
-  // the shared Q / dO tile (with LSE and Delta) of kBufs steps, each buffer
-  // its own array so that the compiler sees that direct loads in flight never
-  // touch the buffer being read
-  struct Buf {
-    T q[Q::kElems];
-    T g[Q::kElems];
-    float l[2 * kQ];  // LSE, Delta
-  };
-  constexpr int kBufs = 4 * (int)sizeof(Buf) <= 160 * 1024 ? 4 : 2;
-  typedef std::conditional_t<(kBufs > 2), Buf, char> Buf23;  // (unused with two buffers)
-  __shared__ __attribute__((aligned(16))) Buf s_b0;
-  __shared__ __attribute__((aligned(16))) Buf s_b1;
-  __shared__ __attribute__((aligned(16))) Buf23 s_b2;
-  __shared__ __attribute__((aligned(16))) Buf23 s_b3;
-  auto buf = [&](auto n) -> auto& {
-    constexpr int kN = decltype(n)::value % kBufs;
-    if constexpr (kN == 0) return s_b0;
-    else if constexpr (kN == 1) return s_b1;
-    else if constexpr (kN == 2) return s_b2;
-    else return s_b3;
-  };
+// -------------------------------------------- dK / dV, fp32, 16 keys a block
+//
+// A block owns 16 keys of one (sequence, KV head); its kWaves waves deal the
+// (query head, 16-row query tile) steps that see them round, each wave with
+// two tile buffers of its own (Q and dO rows, LSE, Delta) filled by untracked
+// direct loads one step ahead: no barrier until the waves' sums are added, in
+// a fixed order, through LDS at the end.  Per step a wave computes on the
+// 16x16x4 fp32 MFMA
+//   S = Q K^T - LSE/scale,  dP = dO V^T - Delta     (rows x keys)
+//   P = exp2(scale log2e S),  dZ = P dP     (masked)
+//   dV^T += dO^T P,  dK^T += Q^T dZ          (d x keys, 16-row blocks of d)
+// The k index of a product is free as long as both operands agree on it: S
+// and dP take elements 16c + 4g + t from lane group g for MFMA t, so a row's
+// operands are 16-byte reads, and the C layout (rows 4g + i in group g) makes
+// P and dZ their own B operands with row 4g + t for MFMA t.
+//
+// Bound by the fp32 MFMA once the chip is full; few sequences leave it idle,
+// and then what counts is the longest chain of steps of a wave.  Blocks of
+// 128 keys, 32 a wave, ran every step of a key in one wave: at 632 x 182 (b =
+// 4, 8/4 heads of 64) 32 blocks took 193 us, and 128-wide heads spilled.
+template <int D>
+struct KvBwdShapeF32 {
+  static constexpr int kWaves = D == 128 ? 4 : 8;  // two 8 KB (16 KB) tile pairs a wave in 160 KB
+  static constexpr int kThreads = 64 * kWaves;
+  static constexpr int kKeys = 16;
+};
 
-  int pair, kt;
-  dkdv_item(blockIdx.x, gridDim.x, a.num_key_tiles, pair, kt);
+// the swizzle of the fp32 tiles' 16-byte chunks: a permutation of 16 rows
+// (row-wise reads of 16 rows at one chunk hit distinct banks) that puts rows
+// 4g + t of the four lane groups in distinct quarters (the transposed reads
+// of 4 rows x 16 columns hit 64 distinct banks)
+__device__ __forceinline__ int swz_f32(int r) { return r & 15; }
+
+template <int D, bool kRuns>
+__global__ __launch_bounds__(KvBwdShapeF32<D>::kThreads, KvBwdShapeF32<D>::kWaves / 4) void prefill_bwd_dkdv_f32_kernel(
+    PrefillBwdArgs a) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  constexpr int kWaves = KvBwdShapeF32<D>::kWaves;
+  constexpr int kQ = 16;                        // query rows per step
+  constexpr int kDB = D / 16;                   // 16-element blocks of d
+  constexpr int kChunks = D / 4;                // 16-byte chunks per row
+  constexpr int kRowsPerLoad = 64 / kChunks;    // rows one wave-wide direct load fills
+  constexpr int kLoads = kQ / kRowsPerLoad;     // direct loads per matrix and step
+  constexpr int kVm = 2 * kLoads + 1;           // (+1: LSE and Delta)
+
+  struct __attribute__((aligned(256))) Buf {
+    float q[kQ * D];
+    float g[kQ * D];
+    float l[64];  // LSE of the rows at 0.., Delta at 32..
+  };
+  __shared__ Buf s_buf[kWaves][2];
+
   const int heads = a.pv.kv_heads;
+  int pair, kt;
+  dkdv_item_heaviest_first(blockIdx.x, gridDim.x / a.num_key_tiles, pair, kt);
   const int g = pair % heads;
   const int b = pair / heads;
 
   const auto sp = span_view<kRuns>(a, b, a.w_eff);
   const int rows = min(sp.rows(), a.q_len);
   const int clen = min(min(sp.clen(), a.pv.max_pages << a.pv.page_shift), a.hat_cap);
-  const int kb0 = kt * kBlockKeys;
-  if (kb0 >= clen) return;  // block-uniform
+  const int kb0 = kt * kQ;
+  if (kb0 >= clen || rows == 0) return;  // block-uniform
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int col = lane & 31, hg = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int gq = lane >> 4, j = lane & 15;  // lane group, column of the 16x16 C layout
   const int hq = a.num_q_heads;
-  const int kb = kb0 + 32 * wave;  // this wave's keys
-  const int key = kb + col;       // this lane's key (C-layout column)
+  const int group = hq / heads;
+  const int gshift = __builtin_ctz(group);  // (a power of two)
+  const int key = kb0 + j;
   const int tau = key < clen ? sp.visible_from(key, a.mask_mode) : INT_MAX;
-  // first row that sees a key of this wave (none: INT_MAX)
-  const int wave_from = kb < clen ? sp.visible_from(kb, a.mask_mode) : INT_MAX;
+  // the first row that sees a key of the block, and the row from which on all
+  // its keys are visible
+  const int q_first = sp.visible_from(kb0, a.mask_mode);
+  const int q_all = sp.visible_from(min(kb0 + 15, clen - 1), a.mask_mode);
 
-  // this lane's K and V rows, the B operands of S = Q K^T and dP = dO V^T,
-  // in registers for every step (a key past the compressed length or without
-  // a page reads page 0 and is zeroed)
-  Frag kf[kQChunks], vf[kQChunks];
+  // K and V of this lane's key, elements 16c + 4gq .. +3 (a key past the
+  // cache or without a page is zero)
+  f32x4 kf[kDB], vf[kDB];
   {
     const int shift = a.pv.page_shift;
-    const int32_t page = a.table[(int64_t)b * a.pv.max_pages + min(key >> shift, a.pv.max_pages - 1)];
-    const bool ok = key < clen && page >= 0 && page < a.pv.num_pages;
-    const int64_t off = page_row<D>(ok ? page : 0, g, key & ((1 << shift) - 1), a.pv) + hg * kPack;
+    const int32_t e = a.table[(int64_t)b * a.pv.max_pages + min(key >> shift, a.pv.max_pages - 1)];
+    const bool ok = key < clen && e >= 0 && e < a.pv.num_pages;
+    const int64_t off = page_row<D>(ok ? e : 0, g, key & ((1 << shift) - 1), a.pv) + 4 * gq;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kc = 0; kc < kQChunks; ++kc) {
-      const Frag k = M::load(static_cast<const T*>(a.k_pages) + off + kc * kStep);
-      const Frag v = M::load(static_cast<const T*>(a.v_pages) + off + kc * kStep);
-      kf[kc] = ok ? k : M::zero();
-      vf[kc] = ok ? v : M::zero();
+    for (int c = 0; c < kDB; ++c) {
+      const f32x4 k = *reinterpret_cast<const f32x4*>(static_cast<const float*>(a.k_pages) + off + 16 * c);
+      const f32x4 v = *reinterpret_cast<const f32x4*>(static_cast<const float*>(a.v_pages) + off + 16 * c);
+      kf[c] = ok ? k : zero;
+      vf[c] = ok ? v : zero;
     }
   }
 
-  // query rows that see some key of the block: from tau(kb0) (tau grows with
-  // c); one step per (query head, 32-row tile) pair
-  const int q_first = sp.visible_from(kb0, a.mask_mode);
+  // steps: (query head, 16-row tile) pairs, last rows first, so that the
+  // blocks of a (sequence, KV head) read the same tiles at the same time
   const int t0 = q_first / kQ, t1 = (rows + kQ - 1) / kQ;
-  const int n_steps = max(t1 - t0, 0) * G;
-
-  // step it into a buffer by direct loads, the block's wave-wide loads dealt
-  // round the waves: Q and dO rows, then LSE (lanes 0-31) and Delta (32-63).
-  // Rows past the end load row 0: finite, never visible.
-  const int lrow = lane / Q::kChunks, lpos = lane % Q::kChunks;
-  auto load_step = [&](int it, Buf& bf) __attribute__((always_inline)) {
-    const int h = g * G + it % G;
-    const int q0 = (t0 + it / G) * kQ;
+  const int n_steps = max(t1 - t0, 0) << gshift;
+  const int rlast = rows - 1;
+  const int lrow = lane / kChunks, lpos = lane % kChunks;
+  const uint64_t row_bytes = (uint64_t)hq * D * sizeof(float);
+  auto load_step = [&](int n, Buf& bf) __attribute__((always_inline)) {
+    const int h = g * group + (n & (group - 1));
+    const int q0 = (t1 - 1 - (n >> gshift)) * kQ;
+    const uint64_t base_off = (((uint64_t)b * a.q_len + q0) * hq + h) * D * sizeof(float);
+    const char* qb = static_cast<const char*>(a.q) + base_off;
+    const char* gb = static_cast<const char*>(a.dout) + base_off;
 #pragma unroll
-    for (int l0 = 0; l0 < Q::kLoads; l0 += kWaves) {
-      const int l = l0 + wave;
-      if (Q::kLoads % kWaves != 0 && l >= Q::kLoads) break;
-      const int r = l * Q::kRowsPerLoad + lrow;
-      const int pr = q0 + r < rows ? q0 + r : 0;
-      const int64_t off = (((int64_t)b * a.q_len + pr) * hq + h) * D + (lpos ^ Q::swz(r)) * kElems16;
-      __builtin_amdgcn_global_load_lds((global_void_ptr)(static_cast<const T*>(a.q) + off),
-                                       (lds_void_ptr)(bf.q + l * Q::kRowsPerLoad * D), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((global_void_ptr)(static_cast<const T*>(a.dout) + off),
-                                       (lds_void_ptr)(bf.g + l * Q::kRowsPerLoad * D), 16, 0, 0);
+    for (int l = 0; l < kLoads; ++l) {
+      const int r = l * kRowsPerLoad + lrow;  // (rows past the end read the last row: finite, and masked)
+      const uint32_t off = (uint32_t)((uint64_t)(min(q0 + r, rlast) - q0) * row_bytes) + ((lpos ^ swz_f32(r)) << 4);
+      lds_dma16(qb, off, lds_addr(bf.q + l * kRowsPerLoad * D));
+      lds_dma16(gb, off, lds_addr(bf.g + l * kRowsPerLoad * D));
     }
-    if (wave == kWaves - 1) {
-      const int pr = q0 + col < rows ? q0 + col : 0;
-      const int64_t stat = ((int64_t)b * hq + h) * a.q_len + pr;
-      __builtin_amdgcn_global_load_lds((global_void_ptr)(hg ? a.delta + stat : a.lse + stat),
-                                       (lds_void_ptr)bf.l, 4, 0, 0);
-    }
+    const float* src = lane < 32 ? a.lse : a.delta;
+    const int64_t stat = ((int64_t)b * hq + h) * a.q_len + min(q0 + j, rlast);
+    lds_dma4(src + stat, lds_addr(bf.l));
   };
 
-  f32x16_t dk[D / 32], dv[D / 32];
+  f32x4 dk[kDB], dv[kDB];
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
+  for (int db = 0; db < kDB; ++db)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) dk[db][i] = dv[db][i] = 0.f;
+    for (int i = 0; i < 4; ++i) dk[db][i] = dv[db][i] = 0.f;
+  const float neg_inv_scale = -1.f / a.scale;
 
-  // loads per wave and step: its share of the Q and dO loads (the last wave
-  // also loads LSE / Delta)
-  constexpr int kMine = 2 * ((Q::kLoads + kWaves - 1) / kWaves);
-  // step n from buffer kPar while the next kBufs - 1 steps load into the others
-  auto step = [&](int n, auto par) __attribute__((always_inline)) {
-    constexpr int kPar = decltype(par)::value;
-    const Buf& bf = buf(par);
-    const T* sq = bf.q;
-    const T* sg = bf.g;
-    const float* sl = bf.l;
-    // this buffer's loads (issued kBufs - 1 steps ago by every wave) have
-    // landed: only the loads of the later steps may remain in flight, kMine
-    // per step (the LSE / Delta load is not counted, so that wave waits a
-    // little longer than it must); then every wave is done with the buffer
-    // the next load refills
-    const int later = min(n_steps - 1 - n, kBufs - 2);
-    if (later >= 2) __builtin_amdgcn_s_waitcnt(wait_vmcnt(2 * kMine));
-    else if (later == 1) __builtin_amdgcn_s_waitcnt(wait_vmcnt(kMine));
-    else __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-    __syncthreads();
-    if (n + kBufs - 1 < n_steps) load_step(n + kBufs - 1, buf(std::integral_constant<int, kPar + kBufs - 1>()));
-    const int q0 = (t0 + n / G) * kQ;
-    if (q0 + kQ <= wave_from) return;  // no row of the tile sees a key of this wave
-
-    // S - LSE/scale and dP - Delta: row = query (8*(i/4) + 4*hg + i%4), column
-    // = this lane's key.  The accumulators start from -LSE/scale and -Delta
-    // of their rows (four consecutive rows at a time), so that P = exp(scale
-    // S - LSE) and dZ = P (dP - Delta) need nothing more per row.
-    f32x16_t s, dp;
-    const float neg_inv_scale = -1.f / a.scale;
+  auto compute = [&](int n, const Buf& bf) __attribute__((always_inline)) {
+    const int q0 = (t1 - 1 - (n >> gshift)) * kQ;
+    // S and dP accumulators start from -LSE/scale and -Delta of their rows
+    const f32x4 lv = *reinterpret_cast<const f32x4*>(bf.l + 4 * gq);
+    const f32x4 dl = *reinterpret_cast<const f32x4*>(bf.l + 32 + 4 * gq);
+    f32x4 s, dp;
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const float4 lv = *reinterpret_cast<const float4*>(sl + 8 * q4 + 4 * hg);
-      const float4 dv4 = *reinterpret_cast<const float4*>(sl + kQ + 8 * q4 + 4 * hg);
-      s[4 * q4] = lv.x * neg_inv_scale; s[4 * q4 + 1] = lv.y * neg_inv_scale;
-      s[4 * q4 + 2] = lv.z * neg_inv_scale; s[4 * q4 + 3] = lv.w * neg_inv_scale;
-      dp[4 * q4] = -dv4.x; dp[4 * q4 + 1] = -dv4.y; dp[4 * q4 + 2] = -dv4.z; dp[4 * q4 + 3] = -dv4.w;
+    for (int i = 0; i < 4; ++i) {
+      s[i] = lv[i] * neg_inv_scale;
+      dp[i] = -dl[i];
     }
 #pragma unroll
-    for (int kc = 0; kc < kQChunks; ++kc) {
-      const int e = hg * kPack + kc * kStep;
-      s = M::mma(tile_a(sq, Q::at(col, e)), kf[kc], s);
-      dp = M::mma(tile_a(sg, Q::at(col, e)), vf[kc], dp);
+    for (int c = 0; c < kDB; ++c) {
+      const int at = j * D + (((4 * c + gq) ^ swz_f32(j)) << 2);
+      const f32x4 qa = *reinterpret_cast<const f32x4*>(bf.q + at);
+      const f32x4 ga = *reinterpret_cast<const f32x4*>(bf.g + at);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[t], kf[c][t], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[t], vf[c][t], dp, 0, 0, 0);
+      }
     }
-    float pr[16], dz[16];
+    float pv[4], zv[4];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int r = 8 * (i / 4) + 4 * hg + (i % 4);
-      const bool vis = q0 + r >= tau && q0 + r < rows;
-      const float e = fast_exp2(s[i] * a.scale_log2);
-      pr[i] = vis ? e : 0.f;
-      dz[i] = vis ? e * dp[i] : 0.f;
+    for (int i = 0; i < 4; ++i) pv[i] = fast_exp2(s[i] * a.scale_log2);
+    if (q0 < q_all || q0 + kQ > rows) {  // uniform: some row or key masked
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = q0 + 4 * gq + i;
+        const bool vis = r >= tau && r < rows;
+        pv[i] = vis ? pv[i] : 0.f;
+        dp[i] = vis ? dp[i] : 0.f;
+      }
     }
-    // dV^T += dO^T P and dK^T += Q^T dZ over the 32 query rows (the row order
-    // of the C layout carried into the transposed reads)
 #pragma unroll
-    for (int kk = 0; kk < kQ / kStep; ++kk) {
-      const Frag pf = M::pack_p(pr + kk * kPack);
-      const Frag zf = M::pack_p(dz + kk * kPack);
+    for (int i = 0; i < 4; ++i) zv[i] = pv[i] * dp[i];
 #pragma unroll
-      for (int db = 0; db < D / 32; ++db) {
-        dv[db] = M::mma(tile_t<D>(sg, kk, db, lane), pf, dv[db]);
-        dk[db] = M::mma(tile_t<D>(sq, kk, db, lane), zf, dk[db]);
+    for (int t = 0; t < 4; ++t) {
+      const int r = 4 * gq + t;
+#pragma unroll
+      for (int db = 0; db < kDB; ++db) {
+        const int at = r * D + (((4 * db + (j >> 2)) ^ swz_f32(r)) << 2) + (j & 3);
+        dv[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf.g[at], pv[t], dv[db], 0, 0, 0);
+        dk[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf.q[at], zv[t], dk[db], 0, 0, 0);
       }
     }
   };
 
-  // the first kBufs - 1 steps, then steps in groups of kBufs (compile-time buffers)
-  if (n_steps > 0) load_step(0, buf(std::integral_constant<int, 0>()));
-  if constexpr (kBufs == 4) {
-    if (n_steps > 1) load_step(1, buf(std::integral_constant<int, 1>()));
-    if (n_steps > 2) load_step(2, buf(std::integral_constant<int, 2>()));
-  }
-  for (int n = 0; n < n_steps; n += kBufs) {
-    step(n, std::integral_constant<int, 0>());
-    if (n + 1 < n_steps) step(n + 1, std::integral_constant<int, 1>());
-    if constexpr (kBufs == 4) {
-      if (n + 2 < n_steps) step(n + 2, std::integral_constant<int, 2>());
-      if (n + 3 < n_steps) step(n + 3, std::integral_constant<int, 3>());
+  // wave w takes steps w, w + kWaves, ...; its own loads only, so a count of
+  // them is all it waits for (the first wait covers the K/V loads too)
+  Buf& b0 = s_buf[wave][0];
+  Buf& b1 = s_buf[wave][1];
+  auto step = [&](int n, Buf& cur, Buf& nxt) __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(63));  // the last step's LDS reads are done before nxt is refilled
+    asm volatile("" ::: "memory");
+    if (n + kWaves < n_steps) {
+      load_step(n + kWaves, nxt);
+      __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(kVm));
+    } else {
+      __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
     }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    compute(n, cur);
+  };
+  if (wave < n_steps) load_step(wave, b0);
+  for (int n = wave; n < n_steps; n += 2 * kWaves) {
+    step(n, b0, b1);
+    if (n + kWaves < n_steps) step(n + kWaves, b1, b0);
   }
 
-  // this lane's key: d = 32 db + 8 (i/4) + 4 hg + i%4, four consecutive at a time
-  if (key >= clen) return;
-  float* dkrow = a.dk_hat + (((int64_t)b * a.hat_cap + key) * heads + g) * D + 4 * hg;
-  float* dvrow = a.dv_hat + (((int64_t)b * a.hat_cap + key) * heads + g) * D + 4 * hg;
-  const float sc = a.scale;
+  // the waves' sums through their own (idle) buffers: plane (dK or dV, 16-row
+  // block of d) of 64 lanes x 4 values, each plane added up by one wave
+  constexpr int kPlanes = 2 * kDB;
+  static_assert(kPlanes * 256 * sizeof(float) <= 2 * sizeof(Buf), "a wave's sums fit its buffers");
+  asm volatile("" ::: "memory");
+  {
+    f32x4* mine = reinterpret_cast<f32x4*>(&s_buf[wave][0]);
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int ig = 0; ig < 4; ++ig) {
-      *reinterpret_cast<float4*>(dkrow + 32 * db + 8 * ig) =
-          make_float4(dk[db][4 * ig] * sc, dk[db][4 * ig + 1] * sc, dk[db][4 * ig + 2] * sc, dk[db][4 * ig + 3] * sc);
-      *reinterpret_cast<float4*>(dvrow + 32 * db + 8 * ig) =
-          make_float4(dv[db][4 * ig], dv[db][4 * ig + 1], dv[db][4 * ig + 2], dv[db][4 * ig + 3]);
+    for (int db = 0; db < kDB; ++db) {
+      mine[(2 * db) * 64 + lane] = dk[db];
+      mine[(2 * db + 1) * 64 + lane] = dv[db];
     }
+  }
+  __syncthreads();
+  if (key >= clen) return;
+  const int64_t row = (((int64_t)b * a.hat_cap + key) * heads + g) * D + 4 * gq;
+#pragma unroll
+  for (int k = 0; k < kPlanes / kWaves; ++k) {
+    const int plane = wave + k * kWaves;  // 2 db + (0: dK, 1: dV)
+    f32x4 sum = reinterpret_cast<const f32x4*>(&s_buf[0][0])[plane * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) sum += reinterpret_cast<const f32x4*>(&s_buf[w][0])[plane * 64 + lane];
+    const bool is_v = plane & 1;
+    const float sc = is_v ? 1.f : a.scale;
+    *reinterpret_cast<float4*>((is_v ? a.dv_hat : a.dk_hat) + row + 16 * (plane >> 1)) =
+        make_float4(sum[0] * sc, sum[1] * sc, sum[2] * sc, sum[3] * sc);
+  }
 }
 
 // ---------------------------------------------------- dQ, bf16, 16 rows a wave
@@ -880,12 +864,18 @@ __global__ __launch_bounds__(DqShape16<G>::kThreads, 3) void prefill_bwd_dq16_ke
 //
 // The bf16 dK/dV kernel on the 16x16x32 MFMA: a wave owns 16 keys, so its K
 // and V operands (16 VGPRs each at d = 128) and its dK^T and dV^T
-// accumulators (32 each) leave room for three waves per SIMD.  A block of four
-// waves owns 64 keys of one (sequence, KV head) and walks the (query head,
-// 32-row query tile) steps that see them; each step's Q, dO, LSE and Delta are
-// staged once in LDS for the four waves by untracked direct loads, two steps
-// ahead in three buffers, as in the forward, and each wave reads its MFMA
-// operands four ahead of the products.  Per step a wave computes
+// accumulators (32 each) leave room for three waves per SIMD.  Four waves form
+// a step group with 64 keys of one (sequence, KV head), and the SG groups of
+// a block own the same keys and deal the (query head, 32-row query tile) steps
+// that see them round, so a block's chain of steps is 1 / SG of its keys'
+// steps; at the end the groups' sums are added through LDS in a fixed order.
+// Each step's Q, dO, LSE and Delta are staged once in LDS for its group by
+// untracked direct loads, two steps ahead in three buffers, as in the
+// forward, and each wave reads its MFMA operands four ahead of the products.
+// (Read eight ahead at two waves per SIMD and SG = 2: 91 us at 1596 x 471, b =
+// 8, against 89 with SG = 3; 32 keys a wave on the 32x32x16 MFMA, which halves
+// the LDS reads, spills at two waves per SIMD: 105 us.)  Per step a wave
+// computes
 //   S  = Q K^T  - LSE/scale    (two 16 x 16 blocks: query rows 0-15, 16-31)
 //   dP = dO V^T - Delta
 //   P = exp2(scale log2e S),  dZ = P dP     (masked)
@@ -895,8 +885,8 @@ __global__ __launch_bounds__(DqShape16<G>::kThreads, 3) void prefill_bwd_dq16_ke
 // rows) in the order k = 8g + t <-> row 4g + t (t < 4), 16 + 4g + t - 4
 // (t >= 4), so P and dZ are their own B operands and dO^T / Q^T come from two
 // transposed LDS reads (rows 4g.., 16 + 4g..) per head-dim block.
-template <int D, int G, bool kRuns>
-__global__ __launch_bounds__(256, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdArgs a) {
+template <int D, bool kRuns, int SG>
+__global__ __launch_bounds__(256 * SG, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdArgs a) {
   typedef bf16_bits T;
   typedef QTile<T, D> Q;
   typedef bf16x8_t Frag;
@@ -914,10 +904,11 @@ __global__ __launch_bounds__(256, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdAr
     T g[Q::kElems];
     float l[2 * kQ];  // LSE, Delta
   };
-  __shared__ Buf s_b0, s_b1, s_b2;
+  __shared__ Buf s_buf[SG][3];  // per step group
 
   int pair, kt;
-  dkdv_item(blockIdx.x, gridDim.x, a.num_key_tiles, pair, kt);
+  if constexpr (SG == 1) dkdv_item(blockIdx.x, gridDim.x, a.num_key_tiles, pair, kt);
+  else dkdv_item_heaviest_first(blockIdx.x, gridDim.x / a.num_key_tiles, pair, kt);
   const int heads = a.pv.kv_heads;
   const int g = pair % heads;
   const int b = pair / heads;
@@ -928,9 +919,12 @@ __global__ __launch_bounds__(256, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdAr
   const int kb0 = kt * kBlockKeys;
   if (kb0 >= clen || rows == 0) return;  // block-uniform
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, bwave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = bwave % kWaves, sg = bwave / kWaves;  // key quarter, step group
   const int gq = lane >> 4, j = lane & 15;  // lane group, column of the 16x16 C layout
   const int hq = a.num_q_heads;
+  const int group = hq / heads;
+  const int gshift = __builtin_ctz(group);  // (a power of two)
   const int kw = kb0 + 16 * wave;   // this wave's first key
   const int key = kw + j;           // this lane's key
   const int tau = key < clen ? sp.visible_from(key, a.mask_mode) : INT_MAX;
@@ -939,29 +933,15 @@ __global__ __launch_bounds__(256, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdAr
   const int wave_from = kw < clen ? sp.visible_from(kw, a.mask_mode) : INT_MAX;
   const int wave_all = kw < clen ? sp.visible_from(min(kw + 15, clen - 1), a.mask_mode) : INT_MAX;
 
-  // K and V operands of this lane's key: elements 32c + 8 gq .. +7 (B operand
-  // layout of S = Q K^T and dP = dO V^T); a key past the cache or without a
-  // page reads a row of page 0 (its column of every product is never stored)
-  Frag kf[kDC], vf[kDC];
-  {
-    const int shift = a.pv.page_shift;
-    const int32_t e = a.table[(int64_t)b * a.pv.max_pages + min(key >> shift, a.pv.max_pages - 1)];
-    const bool ok = key < clen && e >= 0 && e < a.pv.num_pages;
-    const int64_t off = page_row<D>(ok ? e : 0, g, key & ((1 << shift) - 1), a.pv) + 8 * gq;
-    const T* kp = static_cast<const T*>(a.k_pages) + off;
-    const T* vp = static_cast<const T*>(a.v_pages) + off;
-    static_for<kDC>([&](auto c) {
-      constexpr int kC = decltype(c)::value;
-      untracked_load16<kC * 64>(kf[kC], kp);
-      untracked_load16<kC * 64>(vf[kC], vp);
-    });
-  }
-
   // steps: (query head, 32-row tile) pairs from the first tile a key of the
   // block is visible in
   const int q_first = sp.visible_from(kb0, a.mask_mode);
   const int t0 = q_first / kQ, t1 = (rows + kQ - 1) / kQ;
-  const int n_steps = max(t1 - t0, 0) * G;
+  const int all_steps = max(t1 - t0, 0) << gshift;
+  // the group's steps sg, sg + SG, ...; every group takes part in the barriers
+  // of the longest (group 0)
+  const int n_steps = (all_steps - sg + SG - 1) / SG;
+  const int max_steps = (all_steps + SG - 1) / SG;
 
   // Step n's Q and dO rows (rows past the end read the last row: finite, and
   // masked), 16-byte chunks swizzled per row (QTile), plus LSE (lanes 0-31)
@@ -969,8 +949,9 @@ __global__ __launch_bounds__(256, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdAr
   const int lrow = lane / Q::kChunks, lpos = lane % Q::kChunks;
   const int rlast = rows - 1;
   auto load_step = [&](int n, Buf& bf) __attribute__((always_inline)) {
-    const int h = g * G + n % G;
-    const int q0 = (t0 + n / G) * kQ;
+    const int m = n * SG + sg;
+    const int h = g * group + (m & (group - 1));
+    const int q0 = (t1 - 1 - (m >> gshift)) * kQ;
     const int rbase = min(q0, rlast);
     const uint64_t row_bytes = (uint64_t)hq * D * sizeof(T);
     const uint64_t base_off = (((uint64_t)b * a.q_len + rbase) * hq + h) * D * sizeof(T);
@@ -992,6 +973,31 @@ __global__ __launch_bounds__(256, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdAr
       lds_dma4(src + stat, lds_addr(bf.l));
     }
   };
+
+  // prologue: steps 0 and 1 and this wave's K and V operands, in flight
+  // together and waited for together (the K/V loads are the compiler's: it
+  // may move or spill their registers)
+  const int my_vm = kVm + (wave == kWaves - 1 ? 1 : 0);
+  if (n_steps > 0) load_step(0, s_buf[sg][0]);
+  if (n_steps > 1) load_step(1, s_buf[sg][1]);
+  // K and V operands of this lane's key: elements 32c + 8 gq .. +7 (B operand
+  // layout of S = Q K^T and dP = dO V^T); a key past the cache or without a
+  // page reads a row of page 0 (its column of every product is never stored)
+  Frag kf[kDC], vf[kDC];
+  {
+    const int shift = a.pv.page_shift;
+    const int32_t e = a.table[(int64_t)b * a.pv.max_pages + min(key >> shift, a.pv.max_pages - 1)];
+    const bool ok = key < clen && e >= 0 && e < a.pv.num_pages;
+    const int64_t off = page_row<D>(ok ? e : 0, g, key & ((1 << shift) - 1), a.pv) + 8 * gq;
+    const T* kp = static_cast<const T*>(a.k_pages) + off;
+    const T* vp = static_cast<const T*>(a.v_pages) + off;
+#pragma unroll
+    for (int c = 0; c < kDC; ++c) {
+      kf[c] = Mfma<T>::load(kp + 32 * c);
+      vf[c] = Mfma<T>::load(vp + 32 * c);
+    }
+  }
+  bare_barrier<0>();
 
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   f32x4 dk[kDB], dv[kDB];
@@ -1016,7 +1022,7 @@ __global__ __launch_bounds__(256, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdAr
 
   // step n from buffer bf; the loads of steps n+1 and n+2 may be in flight
   auto compute = [&](int n, const Buf& bf) __attribute__((always_inline)) {
-    const int q0 = (t0 + n / G) * kQ;
+    const int q0 = (t1 - 1 - ((n * SG + sg) >> gshift)) * kQ;
     if (q0 + kQ <= wave_from) return;  // no row of the tile sees a key of this wave
     uint32_t ar_q = lds_addr(bf.q) + ar_off, ar_g = lds_addr(bf.g) + ar_off;
     uint32_t at_q = lds_addr(bf.q) + at_off, at_g = lds_addr(bf.g) + at_off;
@@ -1118,11 +1124,6 @@ __global__ __launch_bounds__(256, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdAr
     __builtin_amdgcn_sched_group_barrier(0x008, kAheadT, 1);
   };
 
-  // prologue: this wave's K/V operands, steps 0 and 1; wait for the operands
-  // and step 0 (step 1 may stay in flight)
-  const int my_vm = kVm + (wave == kWaves - 1 ? 1 : 0);
-  if (n_steps > 0) load_step(0, s_b0);
-  if (n_steps > 1) load_step(1, s_b1);
   auto barrier_after = [&](int n) __attribute__((always_inline)) {
     // step n+1's loads landed once only step n+2's are in flight
     if (n + 2 < n_steps) {
@@ -1132,21 +1133,45 @@ __global__ __launch_bounds__(256, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdAr
       bare_barrier<0>();
     }
   };
-  barrier_after(-1);
   auto step = [&](int n, auto par) __attribute__((always_inline)) {
     constexpr int kPar = decltype(par)::value;
-    Buf& cur = kPar == 0 ? s_b0 : kPar == 1 ? s_b1 : s_b2;
-    Buf& nxt2 = kPar == 0 ? s_b2 : kPar == 1 ? s_b0 : s_b1;  // the buffer step n-1 used
-    if (n + 2 < n_steps) load_step(n + 2, nxt2);
-    compute(n, cur);
+    if (n + 2 < n_steps) load_step(n + 2, s_buf[sg][(kPar + 2) % 3]);  // the buffer step n-1 used
+    if (SG == 1 || n < n_steps) compute(n, s_buf[sg][kPar]);
     barrier_after(n);
   };
-  for (int n = 0; n < n_steps; n += 3) {
+  for (int n = 0; n < max_steps; n += 3) {
     step(n, std::integral_constant<int, 0>());
-    if (n + 1 >= n_steps) break;
+    if (n + 1 >= max_steps) break;
     step(n + 1, std::integral_constant<int, 1>());
-    if (n + 2 >= n_steps) break;
+    if (n + 2 >= max_steps) break;
     step(n + 2, std::integral_constant<int, 2>());
+  }
+
+  // The step groups' sums through the idle tile buffers, in a fixed order:
+  // group 0 finishes dK (adding the others' to its own), group 1 dV.
+  if constexpr (SG > 1) {
+    constexpr int kPlane = kWaves * 64;  // f32x4 per 16-row block of d
+    static_assert(2 * (SG - 1) * kDB * kPlane * 16 <= (int)sizeof(s_buf), "the sums fit the buffers");
+    f32x4* const parts = reinterpret_cast<f32x4*>(&s_buf[0][0]);
+    const int at = wave * 64 + lane;
+    if (sg != 0) {
+#pragma unroll
+      for (int db = 0; db < kDB; ++db) parts[((sg - 1) * kDB + db) * kPlane + at] = dk[db];
+    }
+    if (sg != 1) {
+      const int slot = SG - 1 + (sg == 0 ? 0 : sg - 1);
+#pragma unroll
+      for (int db = 0; db < kDB; ++db) parts[(slot * kDB + db) * kPlane + at] = dv[db];
+    }
+    __syncthreads();
+    if (sg > 1) return;
+#pragma unroll
+    for (int o = 0; o < SG - 1; ++o)
+#pragma unroll
+      for (int db = 0; db < kDB; ++db) {
+        if (sg == 0) dk[db] += parts[(o * kDB + db) * kPlane + at];
+        else dv[db] += parts[((SG - 1 + o) * kDB + db) * kPlane + at];
+      }
   }
 
   // lane (gq, j) holds d = 16db + 4gq + i (i < 4) of its key
@@ -1156,32 +1181,54 @@ __global__ __launch_bounds__(256, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdAr
   const float sc = a.scale;
 #pragma unroll
   for (int db = 0; db < kDB; ++db) {
-    *reinterpret_cast<float4*>(dkrow + 16 * db) = make_float4(dk[db][0] * sc, dk[db][1] * sc, dk[db][2] * sc, dk[db][3] * sc);
-    *reinterpret_cast<float4*>(dvrow + 16 * db) = make_float4(dv[db][0], dv[db][1], dv[db][2], dv[db][3]);
+    if (SG == 1 || sg == 0)
+      *reinterpret_cast<float4*>(dkrow + 16 * db) = make_float4(dk[db][0] * sc, dk[db][1] * sc, dk[db][2] * sc, dk[db][3] * sc);
+    if (SG == 1 || sg == 1)
+      *reinterpret_cast<float4*>(dvrow + 16 * db) = make_float4(dv[db][0], dv[db][1], dv[db][2], dv[db][3]);
+  }
+}
+
+template <typename T, int D, bool kRuns>
+hipError_t launch_dkdv(const PrefillBwdArgs& a, int batch, hipStream_t s) {
+  auto run = [&](auto kernel, int keys, int threads) {
+    PrefillBwdArgs c = a;
+    c.num_key_tiles = (a.max_keys + keys - 1) / keys;
+    return launch_struct(kernel, dim3((unsigned)(batch * a.pv.kv_heads * c.num_key_tiles)), dim3(threads), s, c);
+  };
+  if constexpr (sizeof(T) == 4) {
+    return run(prefill_bwd_dkdv_f32_kernel<D, kRuns>, KvBwdShapeF32<D>::kKeys, KvBwdShapeF32<D>::kThreads);
+  } else {
+    // The longest chain of steps, and the blocks, of a 64-key split.  Up to
+    // three blocks a CU all blocks of one step group are resident from the
+    // start and the longest chain sets the time: there three groups a block
+    // cut it (us, one group / three: 512 blocks of <= 100 steps 107 / 89, 640
+    // of 102 93 / 76, 224 of 194 200 / 128, 168 of 184 180 / 123, 120 of 88 at
+    // d = 64 65 / 39, 20 of 16 20.7 / 18.8).  Their one block a CU pays its
+    // prologue and sums in the open, so more blocks, or short chains, keep one
+    // group (2048 of 100 395 / 464, 560 of 24 46 / 54, 44 of 4 7.5 / 8.8).
+    const int64_t chain = (int64_t)(a.num_q_heads / a.pv.kv_heads) * ((a.q_rows + 31) / 32);
+    const int64_t blocks = (int64_t)batch * a.pv.kv_heads * ((a.max_keys + 63) / 64);
+    if ((blocks <= 3 * kCus && chain > 50) || (blocks <= kCus && chain > 12))
+      return run(prefill_bwd_dkdv16_kernel<D, kRuns, 3>, 64, 768);
+    return run(prefill_bwd_dkdv16_kernel<D, kRuns, 1>, 64, 256);
   }
 }
 
 template <typename T, int D, int G, bool kRuns>
-hipError_t launch_bwd_r(const PrefillBwdArgs& a, int batch, hipStream_t s) {
-  const unsigned qitems = (unsigned)(batch * a.pv.kv_heads * a.num_q_tiles);
-  hipError_t e;
+hipError_t launch_dq(const PrefillBwdArgs& a, int batch, hipStream_t s) {
+  const unsigned items = (unsigned)(batch * a.pv.kv_heads * a.num_q_tiles);
   if constexpr (sizeof(T) == 2)
-    e = launch_struct(prefill_bwd_dq16_kernel<D, G, kRuns>, dim3(qitems), dim3(DqShape16<G>::kThreads), s, a);
+    return launch_struct(prefill_bwd_dq16_kernel<D, G, kRuns>, dim3(items), dim3(DqShape16<G>::kThreads), s, a);
   else
-    e = launch_struct(prefill_bwd_dq_kernel<T, D, G, kRuns>, dim3(qitems), dim3(PrefillShape<G>::kThreads), s, a);
-  if (e != hipSuccess) return e;
-  const unsigned kitems = (unsigned)(batch * a.pv.kv_heads * a.num_key_tiles);
-  if constexpr (sizeof(T) == 2)
-    return launch_struct(prefill_bwd_dkdv16_kernel<D, G, kRuns>, dim3(kitems), dim3(256), s, a);
-  else
-    return launch_struct(prefill_bwd_dkdv_kernel<T, D, G, kRuns>, dim3(kitems),
-                         dim3(KvBwdShape<T, D>::kThreads), s, a);
+    return launch_struct(prefill_bwd_dq_kernel<T, D, G, kRuns>, dim3(items), dim3(PrefillShape<G>::kThreads), s, a);
 }
 
 template <typename T, int D, int G>
 hipError_t launch_bwd_g(const PrefillBwdArgs& a, int batch, hipStream_t s) {
-  return a.segs.seg_start ? launch_bwd_r<T, D, G, true>(a, batch, s)
-                          : launch_bwd_r<T, D, G, false>(a, batch, s);
+  const bool runs = a.segs.seg_start != nullptr;
+  const hipError_t e = runs ? launch_dq<T, D, G, true>(a, batch, s) : launch_dq<T, D, G, false>(a, batch, s);
+  if (e != hipSuccess) return e;
+  return runs ? launch_dkdv<T, D, true>(a, batch, s) : launch_dkdv<T, D, false>(a, batch, s);
 }
 
 template <typename T, int D>
@@ -1211,11 +1258,6 @@ int prefill_bwd_rows_per_tile(int dtype, int group) {
     case 4: return PrefillShape<4>::kRows;
     default: return PrefillShape<8>::kRows;
   }
-}
-
-int prefill_bwd_keys_per_block(int dtype, int head_dim) {
-  if (dtype == 1) return 64;  // prefill_bwd_dkdv16_kernel: 16 keys per wave, four waves
-  return head_dim == 128 ? KvBwdShape<float, 128>::kKeys : KvBwdShape<float, 64>::kKeys;
 }
 
 hipError_t launch_prefill_bwd(const PrefillBwdArgs& a, int dtype, int head_dim, int group,

@@ -117,6 +117,22 @@ def check_attention_bwd(case):
         assert torch.isnan(dk[b, L:]).all() and torch.isnan(dv[b, L:]).all()
 
 
+# Sequences at the edges of the dK/dV blocks (16 and 64 keys) and of their
+# 16- and 32-row steps, from fewer steps than a block has waves or step groups
+# to some per group; the longest (13 * 32 rows or more of one KV head, few
+# blocks) takes the bf16 kernel's three step groups.  (From two rows on: the
+# dQ and dK of a single row are 0, which has no relative error.)
+EDGES = [2, 15, 16, 17, 31, 33, 63, 64, 65, 129, 417]
+
+
+@pytest.mark.parametrize("dtype,D,Hq", [("bf16", 128, 1), ("bf16", 64, 2), ("bf16", 128, 8),
+                                        ("f32", 64, 1), ("f32", 64, 8), ("f32", 128, 4)])
+def test_attention_bwd_at_block_edges(dtype, D, Hq):
+    print(f"{dtype} D={D} Hq={Hq}", flush=True)
+    check_attention_bwd(Case(P=[n // 3 for n in EDGES], T=[n - n // 3 for n in EDGES],
+                             N=[0] * len(EDGES), layer=2, l0=5, D=D, Hq=Hq, Hkv=1, dtype=dtype))
+
+
 POOL_CASES = {k: CASES[k] for k in ("bf16-d128", "bf16-d64-g1", "f32-d64", "identity-below-l0",
                                      "prefix-empty", "w8", "w12-three-groups", "zero-gate",
                                      "sharp-gate", "varlen", "long-rows")}
