@@ -412,11 +412,9 @@ int speechkv_prefill_attn_segments(const void* q, int32_t batch, int32_t num_q_h
 
 /*
  * speechkv_pool_prefill_attn - speechkv_pool_kv followed by
- * speechkv_prefill_attn in one launch: the attention reads the raw keys and
- * values and pools each key tile on the fly (Sec. III-C: in training the
- * pooling of Eq. 4 runs inside the forward pass), and the pooled rows are
- * stored into the paged cache as well, so that decoding (or the backward)
- * can follow.
+ * speechkv_prefill_attn in one call (Sec. III-C: in training the pooling of
+ * Eq. 4 runs inside the forward pass); the pooled rows are stored into the
+ * paged cache, so that decoding (or the backward) can follow.
  *
  * The cache, cache_len_out, out and lse receive exactly what the two calls
  * would write, bit for bit: the pooled rows come from the same arithmetic,

@@ -13,7 +13,6 @@
 
 #include "kernels.hpp"
 #include "kernels_bwd.hpp"
-#include "kernels_fused.hpp"
 
 // Split partials of speechkv_decode_attn_noalloc.  Each GPU holds its own
 // copy for the life of the process; every call on that GPU shares it.  The
@@ -617,13 +616,40 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
     for (int j = i + 1; j < 4; ++j)
       if (wr[j] && overlaps(wr[i], wr_n[i], wr[j], wr_n[j])) return SPEECHKV_ERR_ALIAS;
   }
-  const int rows_per_tile = skv::prefill_fused_rows_per_tile(group);
-  // at least one tile per (sequence, head): tile 0 writes cache_len_out
-  int64_t tiles = (spans->max_total_len + rows_per_tile - 1) / rows_per_tile;
-  if (tiles < 1) tiles = 1;
+  const int rows_per_tile = skv::prefill_rows_per_tile(group);
+  const int64_t tiles = (spans->max_total_len + rows_per_tile - 1) / rows_per_tile;
   if ((int64_t)batch * cache->num_kv_heads * tiles > INT32_MAX) return SPEECHKV_ERR_INVALID_ARG;
-  skv::PrefillFusedArgs f;
-  skv::PrefillArgs& a = f.at;
+  // no slot at or past the block table's capacity is stored
+  const int64_t slots = (int64_t)cache->max_pages_per_seq * cache->page_size;
+  const int max_out = spans->max_total_len < slots ? spans->max_total_len : (int)slots;
+  if (skv::pool_grid_blocks(max_out, cache->num_kv_heads, D) > INT32_MAX) return SPEECHKV_ERR_INVALID_ARG;
+  // Pool into the cache, then attend over it: pooling inside the attention
+  // would pool every key tile again for each query block that sees it (1596 x
+  // 471, b = 8: 106 us in one kernel, 14 + 39 us in two; one sequence of 298 x
+  // 53 rows: 14.9 us in one, 11 us in two).
+  skv::PoolArgs pa;
+  pa.k_raw = k_raw;
+  pa.v_raw = v_raw;
+  pa.stride_b = stride_b;
+  pa.stride_s = stride_s;
+  pa.stride_h = stride_h;
+  pa.raw_len = raw_len;
+  pa.prefix_len = spans->prefix_len;
+  pa.speech_len = spans->speech_len;
+  pa.suffix_len = spans->suffix_len;
+  pa.w_eff = layer >= l0 ? w : 1;
+  pa.gate = gate_u;
+  pa.k_pages = cache->k_pages;
+  pa.v_pages = cache->v_pages;
+  pa.table = cache->block_table;
+  pa.pv = view_of(cache);
+  pa.cache_len_out = cache_len_out;
+  pa.max_out = max_out;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const hipError_t e = skv::launch_pool(pa, cache->dtype, D, batch, s);
+  if (e != hipSuccess) return SPEECHKV_ERR_HIP;
+  if (spans->max_total_len == 0) return SPEECHKV_OK;
+  skv::PrefillArgs a;
   a.q = q;
   a.out = out;
   a.lse = lse;
@@ -634,23 +660,13 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
   a.prefix_len = spans->prefix_len;
   a.speech_len = spans->speech_len;
   a.suffix_len = spans->suffix_len;
-  a.w_eff = layer >= l0 ? w : 1;
+  a.w_eff = pa.w_eff;
   a.mask_mode = mask_mode;
   a.q_len = q_len;
   a.num_tiles = (int)tiles;
   a.num_q_heads = num_q_heads;
   a.scale_log2 = scale * 1.4426950408889634f;
-  f.k_pages = cache->k_pages;
-  f.v_pages = cache->v_pages;
-  f.k_raw = k_raw;
-  f.v_raw = v_raw;
-  f.stride_b = stride_b;
-  f.stride_s = stride_s;
-  f.stride_h = stride_h;
-  f.raw_len = raw_len;
-  f.gate = gate_u;
-  f.cache_len_out = cache_len_out;
-  return status_of(skv::launch_prefill_fused(f, D, group, batch, static_cast<hipStream_t>(stream)));
+  return status_of(skv::launch_prefill(a, cache->dtype, D, group, batch, s));
 }
 
 size_t speechkv_prefill_attn_bwd_workspace_bytes(int32_t batch, int32_t num_q_heads, int32_t q_len) {

@@ -380,7 +380,7 @@ def speechkv_pool_prefill_attn(q: torch.Tensor, k_raw: torch.Tensor, v_raw: torc
                                cache_len_out: Optional[torch.Tensor] = None,
                                mask_mode: int = MASK_WINDOW_END, scale: Optional[float] = None,
                                lse: Optional[torch.Tensor] = None, stream=None) -> None:
-    """Pooling and prefill attention in one launch.  q, out: [B, q_len, Hq, D]
+    """Pooling and prefill attention in one call.  q, out: [B, q_len, Hq, D]
     contiguous; k_raw, v_raw: [B, S_raw, Hkv, D] views with a contiguous last
     axis; lse: [B, Hq, q_len] fp32 or None."""
     for x in (q, out) + ((lse,) if lse is not None else ()):
