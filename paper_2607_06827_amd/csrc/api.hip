@@ -521,9 +521,10 @@ static int prefill_attn_impl(const void* q, int32_t batch, int32_t num_q_heads, 
   const Region wr[] = {{out, qo_bytes}, {lse, (int64_t)batch * num_q_heads * q_len * 4}};
   if (aliased(wr, 2, rd, 7)) return SPEECHKV_ERR_ALIAS;
   if (spans->max_total_len == 0) return SPEECHKV_OK;
-  const int rows_per_tile = skv::prefill_rows_per_tile(group);
+  const int rows_per_tile = skv::prefill_rows_per_tile(cache->dtype, group);
   const int64_t tiles = (spans->max_total_len + rows_per_tile - 1) / rows_per_tile;
-  if ((int64_t)batch * cache->num_kv_heads * tiles > INT32_MAX) return SPEECHKV_ERR_INVALID_ARG;
+  if ((int64_t)batch * cache->num_kv_heads * tiles * skv::prefill_blocks_per_tile(cache->dtype, group) > INT32_MAX)
+    return SPEECHKV_ERR_INVALID_ARG;
   skv::PrefillArgs a;
   a.q = q;
   a.out = out;
@@ -538,6 +539,7 @@ static int prefill_attn_impl(const void* q, int32_t batch, int32_t num_q_heads, 
   a.w_eff = layer >= l0 ? w : 1;
   a.mask_mode = mask_mode;
   a.q_len = q_len;
+  a.q_rows = spans->max_total_len;
   a.num_tiles = (int)tiles;
   a.num_q_heads = num_q_heads;
   a.scale_log2 = scale * 1.4426950408889634f;
@@ -616,7 +618,7 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
     for (int j = i + 1; j < 4; ++j)
       if (wr[j] && overlaps(wr[i], wr_n[i], wr[j], wr_n[j])) return SPEECHKV_ERR_ALIAS;
   }
-  const int rows_per_tile = skv::prefill_rows_per_tile(group);
+  const int rows_per_tile = skv::prefill_rows_per_tile(cache->dtype, group);
   const int64_t tiles = (spans->max_total_len + rows_per_tile - 1) / rows_per_tile;
   if ((int64_t)batch * cache->num_kv_heads * tiles > INT32_MAX) return SPEECHKV_ERR_INVALID_ARG;
   // no slot at or past the block table's capacity is stored
@@ -663,6 +665,7 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
   a.w_eff = pa.w_eff;
   a.mask_mode = mask_mode;
   a.q_len = q_len;
+  a.q_rows = spans->max_total_len;
   a.num_tiles = (int)tiles;
   a.num_q_heads = num_q_heads;
   a.scale_log2 = scale * 1.4426950408889634f;
@@ -723,7 +726,7 @@ static int prefill_attn_bwd_impl(const void* q, int32_t batch, int32_t num_q_hea
   const int64_t q_tiles = (spans->max_total_len + rows_per_tile - 1) / rows_per_tile;
   const int64_t keys = spans->max_total_len < hat_capacity ? spans->max_total_len : hat_capacity;
   const int64_t key_tiles = (keys + skv::kMinKeysPerBlock - 1) / skv::kMinKeysPerBlock;
-  if ((int64_t)batch * cache->num_kv_heads * q_tiles > INT32_MAX ||
+  if ((int64_t)batch * cache->num_kv_heads * q_tiles * skv::prefill_blocks_per_tile(cache->dtype, group) > INT32_MAX ||
       (int64_t)batch * cache->num_kv_heads * key_tiles > INT32_MAX)
     return SPEECHKV_ERR_INVALID_ARG;
   skv::PrefillBwdArgs a;

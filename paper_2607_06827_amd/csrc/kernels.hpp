@@ -80,6 +80,7 @@ struct PrefillArgs {
   int w_eff;
   int mask_mode;
   int q_len;
+  int q_rows;     // bound on the rows of a sequence
   int num_tiles;  // query tiles per (sequence, KV head)
   int num_q_heads;
   float scale_log2;
@@ -97,7 +98,12 @@ hipError_t launch_decode(const DecodeArgs& a, int dtype, int head_dim, int group
                          hipStream_t s);
 hipError_t launch_decode_merge(const DecodeArgs& a, int dtype, int head_dim, int num_q_heads,
                                int batch, hipStream_t s);
-int prefill_rows_per_tile(int group);
+int prefill_rows_per_tile(int dtype, int group);
+// The fp32 kernels of prefill_f32.hip take 16 rows of one query head a block,
+// the others a row tile of all the heads of a group: blocks per row tile.
+constexpr int kF32Rows = 16;
+inline int prefill_blocks_per_tile(int dtype, int group) { return dtype == 0 ? group : 1; }
+hipError_t launch_prefill_f32(const PrefillArgs& a, int head_dim, int group, int batch, hipStream_t s);
 hipError_t launch_prefill(const PrefillArgs& a, int dtype, int head_dim, int group, int batch,
                           hipStream_t s);
 

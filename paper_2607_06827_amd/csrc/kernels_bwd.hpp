@@ -69,6 +69,8 @@ struct PoolBwdArgs {
 
 int prefill_bwd_rows_per_tile(int dtype, int group);
 constexpr int kMinKeysPerBlock = 16;  // fewest keys of a dK/dV block
+hipError_t launch_prefill_bwd_dq_f32(const PrefillBwdArgs& a, int head_dim, int group, int batch,
+                                     hipStream_t s);
 hipError_t launch_prefill_bwd(const PrefillBwdArgs& a, int dtype, int head_dim, int group,
                               int batch, hipStream_t s);
 // Slots of one sequence a pooling-backward block covers (a multiple of the

@@ -735,7 +735,9 @@ hipError_t launch_prefill_lds(const PrefillArgs& a, int group, int batch, hipStr
 
 }  // namespace
 
-int prefill_rows_per_tile(int group) {
+namespace {
+
+int shared_tile_rows(int group) {
   switch (group) {
     case 1: return PrefillShape<1>::kRows;
     case 2: return PrefillShape<2>::kRows;
@@ -744,21 +746,35 @@ int prefill_rows_per_tile(int group) {
   }
 }
 
+}  // namespace
+
+int prefill_rows_per_tile(int dtype, int group) { return dtype == 0 ? kF32Rows : shared_tile_rows(group); }
+
 hipError_t launch_prefill(const PrefillArgs& a, int dtype, int head_dim, int group, int batch,
                           hipStream_t s) {
   const bool runs = a.segs.seg_start != nullptr;
-  if (dtype == 1) {
+  if (dtype == 0) {
+    // Blocks of prefill_kernel, whose waves share each K/V tile and take
+    // every key tile of their rows in turn.  Few of them leave SIMDs idle and
+    // wait for the longest chain: there 16-row blocks whose waves deal the key
+    // tiles out are faster (us, shared / dealt, at d = 64: 48 blocks 32 / 13,
+    // 160 23 / 17, 384 90 / 67, 640 42 / 44; at d = 128, where a wave does twice
+    // the work a tile: 320 47 / 50, 440 295 / 324).
+    PrefillArgs c = a;
+    c.num_tiles = (a.q_rows + shared_tile_rows(group) - 1) / shared_tile_rows(group);
+    if ((int64_t)batch * a.pv.kv_heads * c.num_tiles <= (head_dim == 64 ? 512 : 256))
+      return launch_prefill_f32(a, head_dim, group, batch, s);
     if (head_dim == 128)
-      return runs ? launch_prefill_lds<128, true>(a, group, batch, s)
-                  : launch_prefill_lds<128, false>(a, group, batch, s);
-    return runs ? launch_prefill_lds<64, true>(a, group, batch, s)
-                : launch_prefill_lds<64, false>(a, group, batch, s);
+      return runs ? launch_prefill_d<float, 128, true>(c, group, batch, s)
+                  : launch_prefill_d<float, 128, false>(c, group, batch, s);
+    return runs ? launch_prefill_d<float, 64, true>(c, group, batch, s)
+                : launch_prefill_d<float, 64, false>(c, group, batch, s);
   }
   if (head_dim == 128)
-    return runs ? launch_prefill_d<float, 128, true>(a, group, batch, s)
-                : launch_prefill_d<float, 128, false>(a, group, batch, s);
-  return runs ? launch_prefill_d<float, 64, true>(a, group, batch, s)
-              : launch_prefill_d<float, 64, false>(a, group, batch, s);
+    return runs ? launch_prefill_lds<128, true>(a, group, batch, s)
+                : launch_prefill_lds<128, false>(a, group, batch, s);
+  return runs ? launch_prefill_lds<64, true>(a, group, batch, s)
+              : launch_prefill_lds<64, false>(a, group, batch, s);
 }
 
 }  // namespace skv

@@ -30,8 +30,8 @@
 //     S = Q K^T,  dP = dO V^T               (queries x keys, one key per lane)
 //     dV^T += dO^T P,  dK^T += Q^T dZ        (dO^T, Q^T read transposed)
 //   starting S and dP from -LSE/scale and -Delta of their rows.
-// The fp32 kernels run every product on the fp32 MFMA (32x32x2 in dQ, 16x16x4
-// in dK/dV).  The bf16 kernels (further down) keep this split and these
+// The fp32 dK/dV kernel runs every product on the 16x16x4 fp32 MFMA (the fp32
+// dQ kernel is in prefill_f32.hip).  The bf16 kernels keep this split and these
 // formulas on the 16x16x32 bf16 MFMA with small per-wave tiles (16 query rows,
 // or 16 keys, a wave), so that three waves share each SIMD; P and dZ are
 // rounded to bf16 as MFMA operands, every product accumulates in fp32, and
@@ -56,198 +56,6 @@ __device__ __forceinline__ float frag_dot(bf16x8_t x, bf16x8_t y) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) s = __builtin_fmaf((float)x[i], (float)y[i], s);
   return s;
-}
-__device__ __forceinline__ float frag_dot(float x, float y) { return x * y; }
-
-// ------------------------------------------------------------------ dQ
-
-template <typename T, int D, int G, bool kRuns>
-__global__ __launch_bounds__(PrefillShape<G>::kThreads) void prefill_bwd_dq_kernel(PrefillBwdArgs a) {
-  typedef Mfma<T> M;
-  typedef typename M::Frag Frag;
-  constexpr int kThreads = PrefillShape<G>::kThreads;
-  constexpr int kRows = PrefillShape<G>::kRows;
-  constexpr int kKeys = 32;                       // keys per tile
-  constexpr int kPack = M::kPack;
-  constexpr int kStep = 2 * kPack;                // head-dim elements per MFMA
-  constexpr int kQChunks = D / kStep;
-  constexpr int kElems16 = 16 / (int)sizeof(T);   // elements per 16-byte chunk
-  constexpr int kChunksPerRow = D / kElems16;
-  constexpr int kRowK = D + kElems16;             // padded K and V rows (elements)
-  constexpr int kItems = kKeys * kChunksPerRow;   // staging work: (key, 16-byte chunk)
-  constexpr int kItemsPerThread = (kItems + kThreads - 1) / kThreads;
-  constexpr int kTile = kKeys * kRowK;
-
-  __shared__ __attribute__((aligned(16))) T s_buf[2 * 2 * kTile];  // [buffer][K, V]
-
-  // XCD-aware, heaviest-first item order (as in the forward)
-  int pair, tile;
-  query_tile_item(blockIdx.x, gridDim.x, a.num_q_tiles, pair, tile);
-  const int heads = a.pv.kv_heads;
-  const int g = pair % heads;
-  const int b = pair / heads;
-
-  const auto sp = span_view<kRuns>(a, b, a.w_eff);
-  const int rows = min(sp.rows(), a.q_len);
-  const int clen = min(sp.clen(), a.pv.max_pages << a.pv.page_shift);
-  const int p0 = tile * kRows;
-  if (p0 >= rows) return;
-  const int kmax = min(sp.visible(min(p0 + kRows, rows) - 1, a.mask_mode), clen);
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int h = g * G + wave % G;
-  const int col = lane & 31, hg = lane >> 5;
-  const int wrow0 = p0 + (wave / G) * 32;
-  const int p = wrow0 + col;
-  const bool qvalid = p < rows;
-  const int nvis = qvalid ? min(sp.visible(p, a.mask_mode), clen) : 0;
-  const int hq = a.num_q_heads;
-  const int slot_mask = (1 << a.pv.page_shift) - 1;
-
-  f32x16_t acc[D / 32], kbar[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[db][i] = kbar[db][i] = 0.f;
-  float dsum = 0.f;  // sum over this lane's keys of P dP (half of Delta)
-
-  const T* kpool = static_cast<const T*>(a.k_pages);
-  const T* vpool = static_cast<const T*>(a.v_pages);
-  const int ntiles = (kmax + kKeys - 1) / kKeys;
-
-  // K/V staging: the forward's branch-free pipeline (table entries three tiles
-  // ahead, rows two tiles ahead in registers, LDS one tile ahead), both tiles
-  // row-major; rows past the visible range are zero.
-  const int32_t* table_row = a.table + (int64_t)b * a.pv.max_pages;
-  const int64_t num_pages = a.pv.num_pages;
-  const int shift = a.pv.page_shift;
-  int pg[2][kItemsPerThread];
-  uint4 rk[2][kItemsPerThread], rv[2][kItemsPerThread];
-  uint32_t okm[2];
-  auto item_key = [&](int it) { return (tid + it * kThreads) / kChunksPerRow; };
-  auto item_chunk = [&](int it) { return (tid + it * kThreads) % kChunksPerRow; };
-  auto table_load = [&](int kt, int* pgs) {
-#pragma unroll
-    for (int it = 0; it < kItemsPerThread; ++it)
-      pgs[it] = table_row[min((kt * kKeys + item_key(it)) >> shift, a.pv.max_pages - 1)];
-  };
-  auto fetch = [&](int kt, const int* pgs, uint4* rks, uint4* rvs, uint32_t& oks) {
-    oks = 0;
-#pragma unroll
-    for (int it = 0; it < kItemsPerThread; ++it) {
-      const int key = kt * kKeys + item_key(it);
-      const int page = pgs[it];
-      const bool ok = key < kmax && page >= 0 && page < num_pages;
-      oks |= ok ? 1u << it : 0u;
-      const int64_t off = page_row<D>(ok ? page : 0, g, key & slot_mask, a.pv) + item_chunk(it) * kElems16;
-      rks[it] = *reinterpret_cast<const uint4*>(kpool + off);
-      rvs[it] = *reinterpret_cast<const uint4*>(vpool + off);
-    }
-  };
-  auto stage = [&](int buf, const uint4* rks, const uint4* rvs, uint32_t oks) {
-    T* sk = s_buf + buf * 2 * kTile;
-    T* sv = sk + kTile;
-#pragma unroll
-    for (int it = 0; it < kItemsPerThread; ++it) {
-      if (tid + it * kThreads >= kItems) continue;
-      const int key = item_key(it), ch = item_chunk(it);
-      const uint32_t m = 0u - ((oks >> it) & 1u);
-      const uint4 kv = rks[it], vv = rvs[it];
-      *reinterpret_cast<uint4*>(&sk[key * kRowK + ch * kElems16]) = make_uint4(kv.x & m, kv.y & m, kv.z & m, kv.w & m);
-      *reinterpret_cast<uint4*>(&sv[key * kRowK + ch * kElems16]) = make_uint4(vv.x & m, vv.y & m, vv.z & m, vv.w & m);
-    }
-  };
-
-  table_load(0, pg[0]);
-  table_load(1, pg[1]);
-  fetch(0, pg[0], rk[0], rv[0], okm[0]);
-  table_load(2, pg[0]);
-  fetch(1, pg[1], rk[1], rv[1], okm[1]);
-  __builtin_amdgcn_sched_barrier(0);
-  // this lane's query, output and output-gradient row (B operands; rows past
-  // the end read row 0 of the sequence: finite, never stored)
-  Frag qf[kQChunks], gf[kQChunks];
-  const int64_t row_off = (((int64_t)b * a.q_len + (qvalid ? p : 0)) * hq + h) * D + hg * kPack;
-  const T* qrow = static_cast<const T*>(a.q) + row_off;
-  const T* grow = static_cast<const T*>(a.dout) + row_off;
-  const T* orow = static_cast<const T*>(a.out) + row_off;
-  float delta0 = 0.f;  // dO . O from the stored output: the pivot of dZ0
-#pragma unroll
-  for (int kc = 0; kc < kQChunks; ++kc) {
-    qf[kc] = M::load(qrow + kc * kStep);
-    gf[kc] = M::load(grow + kc * kStep);
-    delta0 += frag_dot(gf[kc], M::load(orow + kc * kStep));
-  }
-  const int64_t stat = ((int64_t)b * hq + h) * a.q_len + (qvalid ? p : 0);
-  const float lse2 = a.lse[stat] * kLog2eF;
-  __builtin_amdgcn_sched_barrier(0);
-  stage(0, rk[0], rv[0], okm[0]);
-  __syncthreads();
-  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-  delta0 = partner_sum(delta0);  // the partner lane holds the other half of the row
-
-  auto tile_step = [&](int kt, auto par) {
-    constexpr int kPar = decltype(par)::value;
-    constexpr int kOther = 1 - kPar;
-    table_load(kt + 3, pg[kOther]);
-    fetch(kt + 2, pg[kPar], rk[kPar], rv[kPar], okm[kPar]);
-    const int kb = kt * kKeys;
-    const T* sk = s_buf + kPar * 2 * kTile;
-    const T* sv = sk + kTile;
-    if (kt < ntiles) {
-      // S^T and dP^T: row = key (8*(i/4) + 4*hg + i%4), column = this lane's query
-      f32x16_t st, dpt;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) st[i] = dpt[i] = 0.f;
-      const T* krow = &sk[col * kRowK + hg * kPack];
-      const T* vrow = &sv[col * kRowK + hg * kPack];
-#pragma unroll
-      for (int kc = 0; kc < kQChunks; ++kc) {
-        st = M::mma(M::load(krow + kc * kStep), qf[kc], st);
-        dpt = M::mma(M::load(vrow + kc * kStep), gf[kc], dpt);
-      }
-      float pr[16], dz[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int key = kb + 8 * (i / 4) + 4 * hg + (i % 4);
-        const float e = fast_exp2(__builtin_fmaf(st[i], a.scale_log2, -lse2));
-        pr[i] = key < nvis ? e : 0.f;
-        dz[i] = pr[i] * (dpt[i] - delta0);
-        dsum = __builtin_fmaf(pr[i], dpt[i], dsum);
-      }
-      // dQ^T += K^T dZ0^T and Kbar^T += K^T P^T over the 32 keys of the tile
-#pragma unroll
-      for (int kk = 0; kk < kKeys / kStep; ++kk) {
-        const Frag zf = M::pack_p(dz + kk * kPack);
-        const Frag pf = M::pack_p(pr + kk * kPack);
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db) {
-          const Frag kt = M::template load_v<kRowK>(sk, kk, db, lane);
-          acc[db] = M::mma(kt, zf, acc[db]);
-          kbar[db] = M::mma(kt, pf, kbar[db]);
-        }
-      }
-    }
-    stage(kOther, rk[kOther], rv[kOther], okm[kOther]);
-    __syncthreads();
-  };
-  for (int kt = 0; kt < ntiles; kt += 2) {
-    tile_step(kt, std::integral_constant<int, 0>());
-    tile_step(kt + 1, std::integral_constant<int, 1>());
-  }
-
-  const float delta = partner_sum(dsum);  // sum over all the row's keys of P dP
-  if (!qvalid) return;
-  if (hg == 0) a.delta[stat] = delta;
-  T* drow = static_cast<T*>(a.dq) + (((int64_t)b * a.q_len + p) * hq + h) * D;
-  const float sc = a.scale, fix = delta0 - delta;
-  auto dq_at = [&](int db, int i) { return sc * __builtin_fmaf(fix, kbar[db][i], acc[db][i]); };
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int ig = 0; ig < 4; ++ig)
-      M::store4(drow + db * 32 + 8 * ig + 4 * hg, dq_at(db, 4 * ig), dq_at(db, 4 * ig + 1),
-                dq_at(db, 4 * ig + 2), dq_at(db, 4 * ig + 3));
 }
 
 // --------------------------------------------------------------- dK / dV
@@ -1214,49 +1022,36 @@ hipError_t launch_dkdv(const PrefillBwdArgs& a, int batch, hipStream_t s) {
   }
 }
 
-template <typename T, int D, int G, bool kRuns>
-hipError_t launch_dq(const PrefillBwdArgs& a, int batch, hipStream_t s) {
-  const unsigned items = (unsigned)(batch * a.pv.kv_heads * a.num_q_tiles);
-  if constexpr (sizeof(T) == 2)
-    return launch_struct(prefill_bwd_dq16_kernel<D, G, kRuns>, dim3(items), dim3(DqShape16<G>::kThreads), s, a);
-  else
-    return launch_struct(prefill_bwd_dq_kernel<T, D, G, kRuns>, dim3(items), dim3(PrefillShape<G>::kThreads), s, a);
-}
-
-template <typename T, int D, int G>
-hipError_t launch_bwd_g(const PrefillBwdArgs& a, int batch, hipStream_t s) {
-  const bool runs = a.segs.seg_start != nullptr;
-  const hipError_t e = runs ? launch_dq<T, D, G, true>(a, batch, s) : launch_dq<T, D, G, false>(a, batch, s);
-  if (e != hipSuccess) return e;
-  return runs ? launch_dkdv<T, D, true>(a, batch, s) : launch_dkdv<T, D, false>(a, batch, s);
+template <int D, bool kRuns>
+hipError_t launch_dq16(const PrefillBwdArgs& a, int group, int batch, hipStream_t s) {
+  const dim3 grid((unsigned)(batch * a.pv.kv_heads * a.num_q_tiles));
+  switch (group) {
+    case 1: return launch_struct(prefill_bwd_dq16_kernel<D, 1, kRuns>, grid, dim3(DqShape16<1>::kThreads), s, a);
+    case 2: return launch_struct(prefill_bwd_dq16_kernel<D, 2, kRuns>, grid, dim3(DqShape16<2>::kThreads), s, a);
+    case 4: return launch_struct(prefill_bwd_dq16_kernel<D, 4, kRuns>, grid, dim3(DqShape16<4>::kThreads), s, a);
+    default: return launch_struct(prefill_bwd_dq16_kernel<D, 8, kRuns>, grid, dim3(DqShape16<8>::kThreads), s, a);
+  }
 }
 
 template <typename T, int D>
 hipError_t launch_bwd_d(const PrefillBwdArgs& a, int group, int batch, hipStream_t s) {
-  switch (group) {
-    case 1: return launch_bwd_g<T, D, 1>(a, batch, s);
-    case 2: return launch_bwd_g<T, D, 2>(a, batch, s);
-    case 4: return launch_bwd_g<T, D, 4>(a, batch, s);
-    default: return launch_bwd_g<T, D, 8>(a, batch, s);
-  }
+  const bool runs = a.segs.seg_start != nullptr;
+  hipError_t e;
+  if constexpr (sizeof(T) == 4) e = launch_prefill_bwd_dq_f32(a, D, group, batch, s);
+  else e = runs ? launch_dq16<D, true>(a, group, batch, s) : launch_dq16<D, false>(a, group, batch, s);
+  if (e != hipSuccess) return e;
+  return runs ? launch_dkdv<T, D, true>(a, batch, s) : launch_dkdv<T, D, false>(a, batch, s);
 }
 
 }  // namespace
 
 int prefill_bwd_rows_per_tile(int dtype, int group) {
-  if (dtype == 1) {  // prefill_bwd_dq16_kernel
-    switch (group) {
-      case 1: return DqShape16<1>::kRows;
-      case 2: return DqShape16<2>::kRows;
-      case 4: return DqShape16<4>::kRows;
-      default: return DqShape16<8>::kRows;
-    }
-  }
+  if (dtype == 0) return kF32Rows;
   switch (group) {
-    case 1: return PrefillShape<1>::kRows;
-    case 2: return PrefillShape<2>::kRows;
-    case 4: return PrefillShape<4>::kRows;
-    default: return PrefillShape<8>::kRows;
+    case 1: return DqShape16<1>::kRows;
+    case 2: return DqShape16<2>::kRows;
+    case 4: return DqShape16<4>::kRows;
+    default: return DqShape16<8>::kRows;
   }
 }
 

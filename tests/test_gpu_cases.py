@@ -55,3 +55,25 @@ CASES = {
 def test_case_matches_oracle(name):
     print(f"case {name}", flush=True)
     run_and_check(CASES[name])
+
+
+# fp32 prefill: the kernel of 16-row blocks (few row tiles) at the edges of its
+# row and key tiles, with fewer and more key tiles than waves, and the kernel of
+# shared tiles (more row tiles than 512, or 256 at 128-wide heads).
+F32_EDGES = [1, 2, 15, 16, 17, 33, 63, 64, 65, 130]
+F32_CASES = {
+    "rows-d64": Case(P=F32_EDGES, T=[0] * 10, N=[0] * 10, D=64, Hq=2, Hkv=2, dtype="f32"),
+    "rows-d128-g8": Case(P=[0] * 10, T=F32_EDGES, N=[0] * 10, w=2, D=128, Hq=8, Hkv=1, dtype="f32"),
+    "page8-start-mask": Case(P=[3, 0], T=[120, 37], N=[2, 9], mode=1, D=128, Hq=4, Hkv=2,
+                             page_size=8, dtype="f32"),
+    "shared-d64": Case(P=[i % 5 for i in range(65)], T=[17 + i for i in range(65)],
+                       N=[i % 3 for i in range(65)], D=64, Hq=8, Hkv=8, dtype="f32"),
+    "shared-d128-g4": Case(P=[i % 4 for i in range(65)], T=[9 + i for i in range(65)],
+                           N=[i % 3 for i in range(65)], D=128, Hq=8, Hkv=2, dtype="f32"),
+}
+
+
+@pytest.mark.parametrize("name", sorted(F32_CASES))
+def test_f32_prefill_kernels_match_oracle(name):
+    print(f"case {name}", flush=True)
+    run_and_check(F32_CASES[name])
