@@ -74,16 +74,17 @@ struct QTile {
   static constexpr int kElems = 32 * D;
   // XOR swizzle of the 16-byte chunks of row r.  With 16 chunks per row
   // (bf16, D = 128: a row spans the 64 banks once) the tile is read both
-  // row-wise (16x16x32 A operands: 16 consecutive rows at one chunk per 16
-  // lanes) and transposed (ds_read_b64_tr_b16: 8 consecutive rows x 2
-  // neighbouring chunks per 32 lanes).  ((r & 7) << 1) | ((r >> 3) & 1) is a
-  // permutation of 16 consecutive rows (the row-wise reads hit 16 distinct
-  // chunk positions) whose bits 1-3 differ over 8 consecutive rows (the
-  // transposed reads hit 16 distinct positions).  (The 32x32 layout's
-  // ((r & 3) << 2) | ((r >> 2) & 3) gives rows r and r + 4 the same pair of
-  // positions in the transposed reads: a 2-way bank conflict on each.)
+  // transposed (ds_read_b64_tr_b16: 8 consecutive rows x 2 neighbouring
+  // chunks per 32 lanes, so bits 1-3 differ over 8 consecutive rows) and
+  // row-wise (16x16x32 A operands: lane group g reads rows 0-15 at chunk 4c +
+  // g).  A 16-byte read takes 16 lanes at a time, lanes 0-3, 12-15 of one group
+  // with lanes 4-11 of the next: rows 0-3, 12-15 at one chunk with rows 4-11
+  // at its neighbour.  So the rows whose swizzles differ in bit 0 only are r
+  // and r ^ 12, both of one of these sets, and the 16 positions stay
+  // distinct.  (Paired r with r ^ 8, every row-wise read was a 2-way
+  // conflict: 2.0 conflict cycles per LDS instruction in dQ.)
   static __device__ __forceinline__ int swz(int r) {
-    if constexpr (kChunks == 16) return ((r & 7) << 1) | ((r >> 3) & 1);
+    if constexpr (kChunks == 16) return (((r ^ ((r >> 1) & 4)) & 7) << 1) | ((r >> 3) & 1);
     return r & (kChunks >= 16 ? 15 : kChunks - 1);
   }
   // element e of row r
