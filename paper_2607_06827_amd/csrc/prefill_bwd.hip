@@ -673,14 +673,14 @@ __global__ __launch_bounds__(DqShape16<G>::kThreads, 3) void prefill_bwd_dq16_ke
 //
 // The bf16 dK/dV kernel on the 16x16x32 MFMA: a wave owns 16 keys, so its K
 // and V operands (16 VGPRs each at d = 128) and its dK^T and dV^T
-// accumulators (32 each) leave room for three waves per SIMD.  Four waves form
-// a step group with 64 keys of one (sequence, KV head), and the SG groups of
-// a block own the same keys and deal the (query head, 32-row query tile) steps
+// accumulators (32 each) leave room for three waves per SIMD.  kWaves waves form
+// a step group with 16 kWaves keys of one (sequence, KV head), and the SG groups
+// of a block own the same keys and deal the (query head, 32-row query tile) steps
 // that see them round, so a block's chain of steps is 1 / SG of its keys'
 // steps; at the end the groups' sums are added through LDS in a fixed order.
 // Each step's Q, dO, LSE and Delta are staged once in LDS for its group by
-// untracked direct loads, two steps ahead in three buffers, as in the
-// forward, and each wave reads its MFMA operands four ahead of the products.
+// untracked direct loads, kBufs - 1 steps ahead, as in the forward, and each
+// wave reads its MFMA operands four ahead of the products.
 // (Read eight ahead at two waves per SIMD and SG = 2: 91 us at 1596 x 471, b =
 // 8, against 89 with SG = 3; 32 keys a wave on the 32x32x16 MFMA, which halves
 // the LDS reads, spills at two waves per SIMD: 105 us.)  Per step a wave
@@ -694,12 +694,11 @@ __global__ __launch_bounds__(DqShape16<G>::kThreads, 3) void prefill_bwd_dq16_ke
 // rows) in the order k = 8g + t <-> row 4g + t (t < 4), 16 + 4g + t - 4
 // (t >= 4), so P and dZ are their own B operands and dO^T / Q^T come from two
 // transposed LDS reads (rows 4g.., 16 + 4g..) per head-dim block.
-template <int D, bool kRuns, int SG>
-__global__ __launch_bounds__(256 * SG, 3) void prefill_bwd_dkdv16_kernel(PrefillBwdArgs a) {
+template <int D, bool kRuns, int kWaves, int SG, int kBufs>
+__global__ __launch_bounds__(64 * kWaves * SG, SG == 1 ? 3 : kWaves * SG / 4) void prefill_bwd_dkdv16_kernel(PrefillBwdArgs a) {
   typedef bf16_bits T;
   typedef QTile<T, D> Q;
   typedef bf16x8_t Frag;
-  constexpr int kWaves = 4;
   constexpr int kBlockKeys = 16 * kWaves;
   constexpr int kQ = 32;           // query rows per step
   constexpr int kDC = D / 32;      // K-dim chunks of the S and dP products
@@ -713,7 +712,7 @@ __global__ __launch_bounds__(256 * SG, 3) void prefill_bwd_dkdv16_kernel(Prefill
     T g[Q::kElems];
     float l[2 * kQ];  // LSE, Delta
   };
-  __shared__ Buf s_buf[SG][3];  // per step group
+  __shared__ Buf s_buf[SG][kBufs];  // per step group
 
   int pair, kt;
   if constexpr (SG == 1) dkdv_item(blockIdx.x, gridDim.x, a.num_key_tiles, pair, kt);
@@ -729,7 +728,7 @@ __global__ __launch_bounds__(256 * SG, 3) void prefill_bwd_dkdv16_kernel(Prefill
   if (kb0 >= clen || rows == 0) return;  // block-uniform
 
   const int tid = threadIdx.x, lane = tid & 63, bwave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wave = bwave % kWaves, sg = bwave / kWaves;  // key quarter, step group
+  const int wave = bwave % kWaves, sg = bwave / kWaves;  // place in the step group, step group
   const int gq = lane >> 4, j = lane & 15;  // lane group, column of the 16x16 C layout
   const int hq = a.num_q_heads;
   const int group = hq / heads;
@@ -788,7 +787,7 @@ __global__ __launch_bounds__(256 * SG, 3) void prefill_bwd_dkdv16_kernel(Prefill
   // may move or spill their registers)
   const int my_vm = kVm + (wave == kWaves - 1 ? 1 : 0);
   if (n_steps > 0) load_step(0, s_buf[sg][0]);
-  if (n_steps > 1) load_step(1, s_buf[sg][1]);
+  if (kBufs > 2 && n_steps > 1) load_step(1, s_buf[sg][1]);
   // K and V operands of this lane's key: elements 32c + 8 gq .. +7 (B operand
   // layout of S = Q K^T and dP = dO V^T); a key past the cache or without a
   // page reads a row of page 0 (its column of every product is never stored)
@@ -935,7 +934,7 @@ __global__ __launch_bounds__(256 * SG, 3) void prefill_bwd_dkdv16_kernel(Prefill
 
   auto barrier_after = [&](int n) __attribute__((always_inline)) {
     // step n+1's loads landed once only step n+2's are in flight
-    if (n + 2 < n_steps) {
+    if (kBufs > 2 && n + 2 < n_steps) {
       if (my_vm == kVm) bare_barrier<kVm>();
       else bare_barrier<kVm + 1>();
     } else {
@@ -944,16 +943,19 @@ __global__ __launch_bounds__(256 * SG, 3) void prefill_bwd_dkdv16_kernel(Prefill
   };
   auto step = [&](int n, auto par) __attribute__((always_inline)) {
     constexpr int kPar = decltype(par)::value;
-    if (n + 2 < n_steps) load_step(n + 2, s_buf[sg][(kPar + 2) % 3]);  // the buffer step n-1 used
+    // (into the buffer step n-1 used)
+    if (n + kBufs - 1 < n_steps) load_step(n + kBufs - 1, s_buf[sg][(kPar + kBufs - 1) % kBufs]);
     if (SG == 1 || n < n_steps) compute(n, s_buf[sg][kPar]);
     barrier_after(n);
   };
-  for (int n = 0; n < max_steps; n += 3) {
+  for (int n = 0; n < max_steps; n += kBufs) {
     step(n, std::integral_constant<int, 0>());
     if (n + 1 >= max_steps) break;
     step(n + 1, std::integral_constant<int, 1>());
-    if (n + 2 >= max_steps) break;
-    step(n + 2, std::integral_constant<int, 2>());
+    if constexpr (kBufs > 2) {
+      if (n + 2 >= max_steps) break;
+      step(n + 2, std::integral_constant<int, 2>());
+    }
   }
 
   // The step groups' sums through the idle tile buffers, in a fixed order:
@@ -1009,17 +1011,23 @@ hipError_t launch_dkdv(const PrefillBwdArgs& a, int batch, hipStream_t s) {
   } else {
     // The longest chain of steps, and the blocks, of a 64-key split.  Up to
     // three blocks a CU all blocks of one step group are resident from the
-    // start and the longest chain sets the time: there three groups a block
-    // cut it (us, one group / three: 512 blocks of <= 100 steps 107 / 89, 640
-    // of 102 93 / 76, 224 of 194 200 / 128, 168 of 184 180 / 123, 120 of 88 at
-    // d = 64 65 / 39, 20 of 16 20.7 / 18.8).  Their one block a CU pays its
-    // prologue and sums in the open, so more blocks, or short chains, keep one
-    // group (2048 of 100 395 / 464, 560 of 24 46 / 54, 44 of 4 7.5 / 8.8).
+    // start and the longest chain sets the time, so the steps are dealt out to
+    // more groups: up to a block a CU to eight (d = 64) or four groups of two
+    // waves and 32 keys (us against three groups of four waves: 128 blocks of
+    // <= 196 steps 245 / 158, 144 of 180 109 / 72, 120 of 88 at d = 64 39.7 /
+    // 25.7, 224 of 100 63 / 46, 240 of 68 at d = 64 31.6 / 29.6, 20 of 16 18.4 /
+    // 13.9, 256 of 16 21.4 / 22.0, 448 of 98 76 / 89), up to three to three
+    // groups of four waves and 64 keys (one group / three: 512 of 100 107 / 84,
+    // 640 of 102 93 / 76).  The larger blocks pay their prologue and sums in
+    // the open, so more blocks, or short chains, keep one group (one / three:
+    // 2048 of 100 395 / 464, 560 of 24 46 / 54, 44 of 4 7.5 / 8.8).
     const int64_t chain = (int64_t)(a.num_q_heads / a.pv.kv_heads) * ((a.q_rows + 31) / 32);
     const int64_t blocks = (int64_t)batch * a.pv.kv_heads * ((a.max_keys + 63) / 64);
-    if ((blocks <= 3 * kCus && chain > 50) || (blocks <= kCus && chain > 12))
-      return run(prefill_bwd_dkdv16_kernel<D, kRuns, 3>, 64, 768);
-    return run(prefill_bwd_dkdv16_kernel<D, kRuns, 1>, 64, 256);
+    if (blocks <= kCus && chain > 12)
+      return run(prefill_bwd_dkdv16_kernel<D, kRuns, 2, D == 64 ? 8 : 4, 2>, 32, D == 64 ? 1024 : 512);
+    if (blocks <= 3 * kCus && chain > 50)
+      return run(prefill_bwd_dkdv16_kernel<D, kRuns, 4, 3, 3>, 64, 768);
+    return run(prefill_bwd_dkdv16_kernel<D, kRuns, 4, 1, 3>, 64, 256);
   }
 }
 

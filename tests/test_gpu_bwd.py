@@ -119,18 +119,20 @@ def check_attention_bwd(case):
 
 # Sequences at the edges of the dK/dV blocks (16 and 64 keys) and of their
 # 16- and 32-row steps, from fewer steps than a block has waves or step groups
-# to some per group; the longest (13 * 32 rows or more of one KV head, few
-# blocks) takes the bf16 kernel's three step groups.  (From two rows on: the
+# to some per group.  77 blocks of 14 steps or more take the bf16 kernel's groups
+# of two waves, the 616 blocks of 56 steps (8 KV heads) its three groups of four;
+# the short grids of CASES have one group.  (From two rows on: the
 # dQ and dK of a single row are 0, which has no relative error.)
 EDGES = [2, 15, 16, 17, 31, 33, 63, 64, 65, 129, 417]
 
 
-@pytest.mark.parametrize("dtype,D,Hq", [("bf16", 128, 1), ("bf16", 64, 2), ("bf16", 128, 8),
-                                        ("f32", 64, 1), ("f32", 64, 8), ("f32", 128, 4)])
-def test_attention_bwd_at_block_edges(dtype, D, Hq):
-    print(f"{dtype} D={D} Hq={Hq}", flush=True)
+@pytest.mark.parametrize("dtype,D,Hq,Hkv", [
+    ("bf16", 128, 1, 1), ("bf16", 64, 2, 1), ("bf16", 128, 8, 1), ("bf16", 64, 32, 8),
+    ("bf16", 128, 32, 8), ("f32", 64, 1, 1), ("f32", 64, 8, 1), ("f32", 128, 4, 1)])
+def test_attention_bwd_at_block_edges(dtype, D, Hq, Hkv):
+    print(f"{dtype} D={D} Hq={Hq} Hkv={Hkv}", flush=True)
     check_attention_bwd(Case(P=[n // 3 for n in EDGES], T=[n - n // 3 for n in EDGES],
-                             N=[0] * len(EDGES), layer=2, l0=5, D=D, Hq=Hq, Hkv=1, dtype=dtype))
+                             N=[0] * len(EDGES), layer=2, l0=5, D=D, Hq=Hq, Hkv=Hkv, dtype=dtype))
 
 
 POOL_CASES = {k: CASES[k] for k in ("bf16-d128", "bf16-d64-g1", "f32-d64", "identity-below-l0",
