@@ -276,8 +276,8 @@ def measure_adaptive(base, steps, warmup, num_splits):
 
 
 def measure_fused(base, steps, copies=4):
-    """Pooling and prefill attention as one launch (pooling on the fly inside
-    the attention, Sec. III-C) against the two launches: at the 1596-query
+    """Pooling and prefill attention as one call (speechkv_pool_prefill_attn,
+    Sec. III-C) against the two calls: at the 1596-query
     workload (one layer, `copies` jobs in turn so that no launch finds its
     inputs in the last-level cache) and over the prefill of the whole stack."""
     from paper_2607_06827_amd import inputs
@@ -296,7 +296,7 @@ def measure_fused(base, steps, copies=4):
     ms_fused = time_graph(g_fused, max(2, steps))
     del g_split, g_fused
     log(f"fused pool+prefill ({wl.name}): {us_fused:.1f} us against {us_split:.1f} us as two "
-        f"launches; stack prefill {ms_fused:.3f} ms against {ms_split:.3f} ms")
+        f"calls; stack prefill {ms_fused:.3f} ms against {ms_split:.3f} ms")
     return {"workload": wl.name, "fused_us": us_fused, "split_us": us_split,
             "fused_over_split": us_fused / us_split, "stack_workload": base.wl.name,
             "stack_prefill_fused_ms": ms_fused, "stack_prefill_split_ms": ms_split}

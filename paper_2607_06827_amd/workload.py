@@ -137,9 +137,9 @@ class Job:
                                       self.l0, self.prefill_out, scale=self.scale, stream=stream)
 
     def run_prefill_fused(self, stream=None, layers: Optional[Sequence[int]] = None):
-        """The prefill of every layer as one launch each: the pooling runs on
-        the fly inside the attention (speechkv_pool_prefill_attn), writing the
-        same caches, lengths and outputs as run_prefill."""
+        """The prefill of every layer as one call each
+        (speechkv_pool_prefill_attn), writing the same caches, lengths and
+        outputs as run_prefill."""
         wl = self.wl
         for i, l in enumerate(self.layers):
             if layers is not None and l not in layers:
