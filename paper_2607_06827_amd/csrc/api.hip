@@ -13,6 +13,7 @@
 
 #include "kernels.hpp"
 #include "kernels_bwd.hpp"
+#include "kernels_fused.hpp"
 
 // Split partials of speechkv_decode_attn_noalloc.  Each GPU holds its own
 // copy for the life of the process; every call on that GPU shares it.  The
@@ -24,6 +25,7 @@ static __device__ __align__(256) unsigned char scratch[SPEECHKV_NOALLOC_SCRATCH_
 namespace {
 
 constexpr int kMaxGrid = 65535;
+constexpr int kMaxFusedPairs = 128;  // (sequence, KV head) pairs of the one-kernel pool + prefill
 constexpr int kMaxRows = 2147483647 - SPEECHKV_MAX_WINDOW;  // ceil(T / w) stays in int32
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -617,6 +619,46 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
       if (rd[j] && overlaps(wr[i], wr_n[i], rd[j], rd_n[j])) return SPEECHKV_ERR_ALIAS;
     for (int j = i + 1; j < 4; ++j)
       if (wr[j] && overlaps(wr[i], wr_n[i], wr[j], wr_n[j])) return SPEECHKV_ERR_ALIAS;
+  }
+  // Below l0 pooling is a copy: where at most two blocks of 256 / group rows
+  // read a key tile, and the blocks fit the chip at once, one kernel that
+  // copies its tiles on the fly saves a launch (31 sequences of 165 rows, 8/4
+  // heads of 64: 12.0 us against 13.5; 64 sequences, 16/8 heads of 128: 66.5 us
+  // against 46.5).
+  const int fused_rows = skv::prefill_fused_rows_per_tile(group);
+  int64_t fused_tiles = (spans->max_total_len + fused_rows - 1) / fused_rows;
+  if (fused_tiles < 1) fused_tiles = 1;  // (tile 0 writes cache_len_out)
+  if ((layer < l0 || w == 1) && fused_tiles <= 2 && (int64_t)batch * cache->num_kv_heads <= kMaxFusedPairs) {
+    skv::PrefillFusedArgs f;
+    skv::PrefillArgs& a = f.at;
+    a.q = q;
+    a.out = out;
+    a.lse = lse;
+    a.k_pages = cache->k_pages;
+    a.v_pages = cache->v_pages;
+    a.table = cache->block_table;
+    a.pv = view_of(cache);
+    a.prefix_len = spans->prefix_len;
+    a.speech_len = spans->speech_len;
+    a.suffix_len = spans->suffix_len;
+    a.w_eff = layer >= l0 ? w : 1;
+    a.mask_mode = mask_mode;
+    a.q_len = q_len;
+    a.q_rows = spans->max_total_len;
+    a.num_tiles = (int)fused_tiles;
+    a.num_q_heads = num_q_heads;
+    a.scale_log2 = scale * 1.4426950408889634f;
+    f.k_pages = cache->k_pages;
+    f.v_pages = cache->v_pages;
+    f.k_raw = k_raw;
+    f.v_raw = v_raw;
+    f.stride_b = stride_b;
+    f.stride_s = stride_s;
+    f.stride_h = stride_h;
+    f.raw_len = raw_len;
+    f.gate = gate_u;
+    f.cache_len_out = cache_len_out;
+    return status_of(skv::launch_prefill_fused(f, D, group, batch, static_cast<hipStream_t>(stream)));
   }
   const int rows_per_tile = skv::prefill_rows_per_tile(cache->dtype, group);
   const int64_t tiles = (spans->max_total_len + rows_per_tile - 1) / rows_per_tile;

@@ -98,6 +98,7 @@ struct Mfma<float> {
 // ------------------------------------------------- LDS staging and waits
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
+typedef __attribute__((address_space(1))) void* global_void_ptr;
 
 // Byte address of an LDS object (the 32-bit LDS address space).
 __device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(uintptr_t)(lds_void_ptr)p; }

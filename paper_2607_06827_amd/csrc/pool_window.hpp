@@ -3,7 +3,9 @@
 // lane 8 consecutive elements of the key and value rows.  The window's
 // frames are taken in groups of four; the softmax over the gate logits
 // u . k_j runs online over the groups (log2 units), and the same weights pool
-// the keys and the values.
+// the keys and the values.  Both the pooling kernel and the prefill kernel
+// that pools its key tiles on the fly use these steps, so the two produce the
+// same bits for every pooled row.
 #pragma once
 
 #include "common.hpp"
@@ -30,8 +32,8 @@ struct WindowPool {
   __device__ __forceinline__ void add4(const Chunk<T> (&kc)[4], const Chunk<T> (&vc)[4],
                                        const float (&u)[8], int f0, int frames) {
     // every operation rounds on its own (only the explicit fmaf are fused),
-    // whatever code surrounds the call: every instance of the kernel then
-    // pools a row to the same bits
+    // whatever code surrounds the call: the two kernels that use these steps
+    // then agree bit for bit
 #pragma clang fp contract(off)
     // (rows are converted to fp32 where they are used, which is exact, so
     // that four converted rows never need to be live at once)

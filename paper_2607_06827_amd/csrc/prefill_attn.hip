@@ -45,6 +45,8 @@
 
 #include "attn_mfma.hpp"
 #include "kernels.hpp"
+#include "kernels_fused.hpp"
+#include "pool_window.hpp"
 
 namespace skv {
 
@@ -711,6 +713,239 @@ __global__ __launch_bounds__(PrefillShape<G>::kThreads, 3) void prefill_kernel_l
   finish_rows<D>(o, m_run, l_run, kWaves <= 6 ? so : nullptr, a, b, h, wrow0, rows, lane);
 }
 
+// Block shape of the pooling variant: eight waves whatever the group size, so
+// a block owns 256/G query rows.  Every block pools each key tile it reads,
+// so taller blocks pool each tile fewer times over the whole grid, and eight
+// waves share the work of a tile (one pass of D/8-lane units at D = 128).
+template <int G>
+struct FusedShape {
+  static constexpr int kRowBlocks = 8 / G;
+  static constexpr int kWaves = 8;
+  static constexpr int kThreads = 512;
+  static constexpr int kRows = 32 * kRowBlocks;
+};
+
+// bf16 prefill that reads the raw K/V and pools each key tile on the fly
+// (Sec. III-C) with the pooling kernel's steps (pool_window.hpp), D/8 lanes
+// per (slot, head) unit: the first four frames of every window of tile t+1
+// are loaded before the MFMAs of tile t and pooled after them, straight into
+// the other of two LDS buffers in the layout the direct loads give.  The
+// block holding a sequence's last query rows (which see every key) also
+// stores each pooled row into the paged cache, and pools the rows no query
+// sees, so the cache ends up as the pooling kernel would have written it.
+// Two waves per SIMD: the first frames of the next tile's windows are held
+// in registers across a step.
+template <int D, int G>
+__global__ __launch_bounds__(FusedShape<G>::kThreads, 2) void prefill_kernel_fused(PrefillFusedArgs args) {
+  const PrefillArgs& a = args.at;
+  typedef bf16_bits T;
+  typedef Mfma<T> M;
+  typedef M::Frag Frag;
+  typedef LdsSwz<D> Swz;
+  constexpr int kWaves = FusedShape<G>::kWaves;
+  constexpr int kRows = FusedShape<G>::kRows;
+  constexpr int kKeys = 32;                        // keys per tile
+  constexpr int kQChunks = D / 16;
+  constexpr int kTile = kKeys * D;                 // elements of one tile
+
+  __shared__ __attribute__((aligned(256))) T s_k0[kTile];
+  __shared__ __attribute__((aligned(256))) T s_k1[kTile];
+  __shared__ __attribute__((aligned(256))) T s_v0[kTile];
+  __shared__ __attribute__((aligned(256))) T s_v1[kTile];
+
+  // XCD-aware, heaviest-first item order
+  int pair, tile;
+  query_tile_item(blockIdx.x, gridDim.x, a.num_tiles, pair, tile);
+  const int heads = a.pv.kv_heads;
+  const int g = pair % heads;
+  const int b = pair / heads;
+
+  const int w = a.w_eff;
+  const auto sp = span_view<false>(a, b, w);
+  const int rows = min(sp.rows(), a.q_len);
+  const int clen = min(sp.clen(), a.pv.max_pages << a.pv.page_shift);
+  const int p0 = tile * kRows;
+  if (tile == 0 && g == 0 && threadIdx.x == 0 && args.cache_len_out) args.cache_len_out[b] = sp.clen();
+  if (p0 >= rows) return;
+  const int kmax = min(sp.visible(min(p0 + kRows, rows) - 1, a.mask_mode), clen);
+  const int kclamp = max(kmax - 1, 0);  // last visible key: the row pooled for keys past kmax
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = g * G + wave % G;
+  const int col = lane & 31, hg = lane >> 5;
+  const int wrow0 = p0 + (wave / G) * 32;  // first row of this wave
+  const int p = wrow0 + col;
+  const bool qvalid = p < rows;
+  const int nvis = qvalid ? min(sp.visible(p, a.mask_mode), clen) : 0;
+  const int nvis_lo = wrow0 < rows ? min(sp.visible(wrow0, a.mask_mode), clen) : 0;
+  const int hq = a.num_q_heads;
+  const int slot_mask = (1 << a.pv.page_shift) - 1;
+  const int shift = a.pv.page_shift;
+  const int64_t num_pages = a.pv.num_pages;
+  const int32_t* table_row = a.table + (int64_t)b * a.pv.max_pages;
+  const int ntiles = (kmax + kKeys - 1) / kKeys;
+
+  // on-the-fly pooling: D/8 lanes per (slot, head) unit, one unit per key of
+  // the tile; the first kPoolWaves waves pool, lane pj-th chunk of unit
+  // pslot.  The first four frames of each unit's window are staged by direct
+  // loads into this wave's own LDS area (lane i's 16 bytes of frame t at K:
+  // 2t KB + 16 i, V: 2t+1 KB + 16 i), so they cost no registers across the
+  // MFMAs and each lane reads back only what it loaded.
+  constexpr int kLanes = D / 8;
+  constexpr int kPoolWaves = kKeys / (64 / kLanes);
+  static_assert(kPoolWaves <= kWaves, "one pass of the pooling waves covers a tile");
+  const int pj = lane % kLanes;
+  const int pslot = wave * (64 / kLanes) + lane / kLanes;
+  const bool pool_wave = wave < kPoolWaves;  // uniform over the wave
+  const bool writer = p0 + kRows >= rows;   // holds the last rows: sees every key
+  int fsrc = 0, ffr = 1, fent = 0;          // the unit's first raw row, frames, page
+  float u[8];
+  __shared__ __attribute__((aligned(16))) T s_stage[kPoolWaves * 8 * 512];
+  T* const stage = s_stage + (pool_wave ? wave : 0) * 8 * 512;
+  const T* kr = static_cast<const T*>(args.k_raw) + b * args.stride_b + g * args.stride_h + 8 * pj;
+  const T* vr = static_cast<const T*>(args.v_raw) + b * args.stride_b + g * args.stride_h + 8 * pj;
+  const int64_t raw_stride = args.stride_s;
+  const int raw_last = args.raw_len - 1;
+  if (args.gate) {  // without a gate every logit is 0 (uniform averaging)
+    const float4* gp = reinterpret_cast<const float4*>(args.gate + (int64_t)g * D + 8 * pj);
+    const float4 u0 = gp[0], u1 = gp[1];
+    u[0] = u0.x; u[1] = u0.y; u[2] = u0.z; u[3] = u0.w;
+    u[4] = u1.x; u[5] = u1.y; u[6] = u1.z; u[7] = u1.w;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) u[i] = 0.f;
+  }
+  auto raw_at = [&](int s) __attribute__((always_inline)) { return (int64_t)min(s, raw_last) * raw_stride; };
+  // stage the first four frames of unit (slot min(c0 + pslot, cmax), this
+  // head); frames past a window repeat its last one; w = 1 needs one frame
+  auto pool_fetch = [&](int c0, int cmax) __attribute__((always_inline)) {
+    if (!pool_wave) return;
+    const int c = min(c0 + pslot, cmax);
+    const SlotSource sl = sp.slot(c);
+    fsrc = sl.first;
+    ffr = sl.frames;
+    fent = writer ? table_row[min(c >> shift, a.pv.max_pages - 1)] : 0;
+    const int nt = w == 1 ? 1 : 4;  // uniform
+    for (int t = 0; t < nt; ++t) {
+      const int64_t o = raw_at(sl.first + min(t, sl.frames - 1));
+      __builtin_amdgcn_global_load_lds((global_void_ptr)(kr + o), (lds_void_ptr)(stage + 2 * t * 512), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((global_void_ptr)(vr + o), (lds_void_ptr)(stage + (2 * t + 1) * 512), 16, 0, 0);
+    }
+  };
+  // the unit's pooled rows from the staged frames (and the later frames of
+  // windows longer than four); a text row or one-frame window is its raw row
+  auto pool_rows = [&](Chunk<T>& ko, Chunk<T>& vo) __attribute__((always_inline)) {
+    // the wave's own direct loads must have landed before it reads them back:
+    // the compiler does not order LDS-DMA writes against later LDS reads, so
+    // wait explicitly, fenced on both sides for the optimiser and scheduler
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    Chunk<T> kc[4], vc[4];
+    const int nt = w == 1 ? 1 : 4;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (t < nt) {
+        kc[t].raw = *reinterpret_cast<const uint4*>(stage + 2 * t * 512 + 8 * lane);
+        vc[t].raw = *reinterpret_cast<const uint4*>(stage + (2 * t + 1) * 512 + 8 * lane);
+      }
+    }
+    ko = kc[0];
+    vo = vc[0];
+    if (w > 1) {
+      WindowPool<T, kLanes> wp;
+      wp.init();
+      wp.template add4<true>(kc, vc, u, 0, ffr);
+      for (int f0 = 4; f0 < ffr; f0 += 4) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int64_t o = raw_at(fsrc + min(f0 + t, ffr - 1));
+          kc[t].load(kr + o);
+          vc[t].load(vr + o);
+        }
+        wp.template add4<true>(kc, vc, u, f0, ffr);
+      }
+      Chunk<T> pk, pv;
+      wp.finish(pk, pv);
+      if (ffr > 1) {
+        ko = pk;
+        vo = pv;
+      }
+    }
+  };
+  // cache row c of this head, when it exists, has a valid page and its
+  // source rows lie inside the raw tensor (as the pooling kernel checks)
+  auto cache_store = [&](int c, const Chunk<T>& ko, const Chunk<T>& vo) __attribute__((always_inline)) {
+    if (c < clen && fent >= 0 && fent < num_pages && fsrc + ffr <= raw_last + 1) {
+      const int64_t off = page_row<D>(fent, g, c & slot_mask, a.pv) + 8 * pj;
+      ko.store(static_cast<T*>(args.k_pages) + off);
+      vo.store(static_cast<T*>(args.v_pages) + off);
+    }
+  };
+  // pool key tile kt into LDS; the writer also stores its visible rows
+  auto pool_tile = [&](int kt, T* sk, T* sv) __attribute__((always_inline)) {
+    if (!pool_wave) return;
+    Chunk<T> ko, vo;
+    pool_rows(ko, vo);
+    const int r = pslot;
+    ko.store(sk + r * D + ((pj ^ Swz::k(r)) << 3));
+    vo.store(sv + r * D + ((pj ^ Swz::v(r)) << 3));
+    if (writer && kt * kKeys + r < kmax) cache_store(kt * kKeys + r, ko, vo);
+  };
+
+  f32x16_t o[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
+  float m_run = neg_inf(), l_run = 0.f;
+
+  // prologue: stage tile 0's frames, load this lane's query row (rows past
+  // the end read row 0: finite, never stored), pool tile 0
+  if (ntiles > 0) pool_fetch(0, kclamp);
+  __builtin_amdgcn_sched_barrier(0);
+  Frag qf[kQChunks];
+  {
+    const T* qrow = static_cast<const T*>(a.q) + (((int64_t)b * a.q_len + (qvalid ? p : 0)) * hq + h) * D;
+#pragma unroll
+    for (int kc = 0; kc < kQChunks; ++kc) qf[kc] = M::load(qrow + kc * 16 + hg * 8);
+  }
+  if (ntiles > 0) pool_tile(0, s_k0, s_v0);
+  __syncthreads();
+
+  // step kt: stage the frames of tile kt+1, attend to tile kt, pool tile kt+1
+  // into the other buffer; kPar = kt & 1 selects buffers at compile time
+  auto tile_step = [&](int kt, auto par) {
+    constexpr int kPar = decltype(par)::value;
+    T* const sk = kPar ? s_k1 : s_k0;
+    T* const sv = kPar ? s_v1 : s_v0;
+    const bool pool_next = kt + 1 < ntiles;  // uniform
+    if (pool_next) pool_fetch((kt + 1) * kKeys, kclamp);  // pooled after this tile's MFMAs
+    if (kt < ntiles) attend_tile<D>(sk, sv, qf, o, m_run, l_run, kt * kKeys, nvis, nvis_lo, lane, a.scale_log2);
+    if (pool_next) pool_tile(kt + 1, kPar ? s_k0 : s_k1, kPar ? s_v0 : s_v1);
+    __syncthreads();
+  };
+  for (int kt = 0; kt < ntiles; kt += 2) {
+    tile_step(kt, std::integral_constant<int, 0>());
+    tile_step(kt + 1, std::integral_constant<int, 1>());
+  }
+  // cache rows no query of this sequence sees: pooled and stored by the writer
+  if (writer) {
+    for (int c0 = kmax; c0 < clen; c0 += kKeys) {
+      pool_fetch(c0, clen - 1);
+      if (pool_wave) {
+        Chunk<T> ko, vo;
+        pool_rows(ko, vo);
+        cache_store(c0 + pslot, ko, vo);
+      }
+    }
+  }
+  static_assert(kWaves > 4, "eight waves store their rows from the C layout");
+  finish_rows<D>(o, m_run, l_run, nullptr, a, b, h, wrow0, rows, lane);
+}
+
 template <typename T, int D, bool kRuns>
 hipError_t launch_prefill_d(const PrefillArgs& a, int group, int batch, hipStream_t s) {
   const unsigned items = (unsigned)(batch * a.pv.kv_heads * a.num_tiles);
@@ -730,6 +965,18 @@ hipError_t launch_prefill_lds(const PrefillArgs& a, int group, int batch, hipStr
     case 2: return launch_struct(prefill_kernel_lds<D, 2, kRuns>, dim3(items), dim3(PrefillShape<2>::kThreads), s, a);
     case 4: return launch_struct(prefill_kernel_lds<D, 4, kRuns>, dim3(items), dim3(PrefillShape<4>::kThreads), s, a);
     default: return launch_struct(prefill_kernel_lds<D, 8, kRuns>, dim3(items), dim3(PrefillShape<8>::kThreads), s, a);
+  }
+}
+
+template <int D>
+hipError_t launch_prefill_fused_d(const PrefillFusedArgs& args, int group, int batch, hipStream_t s) {
+  const PrefillArgs& a = args.at;
+  const unsigned items = (unsigned)(batch * a.pv.kv_heads * a.num_tiles);
+  switch (group) {
+    case 1: return launch_struct(prefill_kernel_fused<D, 1>, dim3(items), dim3(FusedShape<1>::kThreads), s, args);
+    case 2: return launch_struct(prefill_kernel_fused<D, 2>, dim3(items), dim3(FusedShape<2>::kThreads), s, args);
+    case 4: return launch_struct(prefill_kernel_fused<D, 4>, dim3(items), dim3(FusedShape<4>::kThreads), s, args);
+    default: return launch_struct(prefill_kernel_fused<D, 8>, dim3(items), dim3(FusedShape<8>::kThreads), s, args);
   }
 }
 
@@ -775,6 +1022,21 @@ hipError_t launch_prefill(const PrefillArgs& a, int dtype, int head_dim, int gro
                 : launch_prefill_lds<128, false>(a, group, batch, s);
   return runs ? launch_prefill_lds<64, true>(a, group, batch, s)
               : launch_prefill_lds<64, false>(a, group, batch, s);
+}
+
+int prefill_fused_rows_per_tile(int group) {
+  switch (group) {
+    case 1: return FusedShape<1>::kRows;
+    case 2: return FusedShape<2>::kRows;
+    case 4: return FusedShape<4>::kRows;
+    default: return FusedShape<8>::kRows;
+  }
+}
+
+hipError_t launch_prefill_fused(const PrefillFusedArgs& a, int head_dim, int group, int batch,
+                                hipStream_t s) {
+  if (head_dim == 128) return launch_prefill_fused_d<128>(a, group, batch, s);
+  return launch_prefill_fused_d<64>(a, group, batch, s);
 }
 
 }  // namespace skv
