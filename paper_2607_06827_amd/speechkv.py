@@ -63,7 +63,8 @@ class _Segments(ctypes.Structure):
 
 # The descriptions above as packed bytes, passed by address: filling a cache
 # description takes 1.0 us instead of 1.7 with a ctypes structure, and a
-# decoding step of one sequence is bound by this path.
+# decoding step of one sequence is bound by this path.  ctypes then takes any
+# of them for any other, so each _c below checks the type of its object.
 _pack_paged_kv = struct.Struct("@PPPiiiiii").pack
 _pack_spans = struct.Struct("@PPPii").pack
 _pack_segments = struct.Struct("@PPPiii").pack
@@ -157,6 +158,8 @@ class PagedKV:
     block_table: torch.Tensor
 
     def _c(self) -> bytes:
+        if not isinstance(self, PagedKV):
+            raise TypeError(f"expected a PagedKV, not {type(self).__name__}")
         k, v, t = self.k_pages, self.v_pages, self.block_table
         if not (k.is_contiguous() and v.is_contiguous() and t.is_contiguous()):
             raise ValueError("paged cache tensors must be contiguous")
@@ -182,6 +185,8 @@ class Spans:
     max_total_len: int
 
     def _c(self) -> bytes:
+        if not isinstance(self, Spans):
+            raise TypeError(f"expected Spans, not {type(self).__name__}")
         for x in (self.prefix_len, self.speech_len, self.suffix_len):
             if x.dtype != torch.int32 or not x.is_contiguous():
                 raise ValueError("span lengths must be contiguous int32 tensors")
@@ -203,6 +208,8 @@ class Segments:
     max_total_len: int
 
     def _c(self) -> bytes:
+        if not isinstance(self, Segments):
+            raise TypeError(f"expected Segments, not {type(self).__name__}")
         for x in (self.seg_start, self.text_len, self.speech_len):
             if x.dtype != torch.int32 or not x.is_contiguous():
                 raise ValueError("segment tables must be contiguous int32 tensors")
@@ -259,8 +266,8 @@ def speechkv_pool_kv(k_raw: torch.Tensor, v_raw: torch.Tensor, spans: Spans, w: 
     if k_raw.dim() != 4 or k_raw.stride(3) != 1:
         raise ValueError("raw K/V must be [B, S, Hkv, D] with a contiguous last axis")
     sb, ss, sh, _ = k_raw.stride()
-    c = cache._c()
-    s = spans._c()
+    c = PagedKV._c(cache)
+    s = Spans._c(spans)
     st = _lib.speechkv_pool_kv(k_raw.data_ptr(), v_raw.data_ptr(), sb, ss, sh, k_raw.shape[0],
                                k_raw.shape[1], s, w, _ptr(gate_u), layer, l0,
                                c, _ptr(cache_len_out), _stream(stream))
@@ -276,8 +283,8 @@ def speechkv_pool_kv_segments(k_raw: torch.Tensor, v_raw: torch.Tensor, segs: Se
     if k_raw.dim() != 4 or k_raw.stride(3) != 1:
         raise ValueError("raw K/V must be [B, S, Hkv, D] with a contiguous last axis")
     sb, ss, sh, _ = k_raw.stride()
-    c = cache._c()
-    g = segs._c()
+    c = PagedKV._c(cache)
+    g = Segments._c(segs)
     st = _lib.speechkv_pool_kv_segments(k_raw.data_ptr(), v_raw.data_ptr(), sb, ss, sh,
                                         k_raw.shape[0], k_raw.shape[1], g, w,
                                         _ptr(gate_u), layer, l0, c,
@@ -296,8 +303,8 @@ def speechkv_prefill_attn_segments(q: torch.Tensor, cache: PagedKV, segs: Segmen
     B, q_len, Hq, D = q.shape
     if scale is None:
         scale = D ** -0.5
-    c = cache._c()
-    g = segs._c()
+    c = PagedKV._c(cache)
+    g = Segments._c(segs)
     st = _lib.speechkv_prefill_attn_segments(q.data_ptr(), B, Hq, q_len, c,
                                              g, w, layer, l0, mask_mode, scale,
                                              out.data_ptr(), _ptr(lse), _stream(stream))
@@ -321,7 +328,7 @@ def speechkv_pool_hidden(h: torch.Tensor, spans: Spans, w: int, gate_u: Optional
         raise ValueError("h and out must be [B, S, hidden] with a contiguous last axis")
     if h.dtype != out.dtype or h.shape[0] != out.shape[0] or h.shape[2] != out.shape[2]:
         raise ValueError("h and out must agree in dtype, batch and hidden size")
-    s = spans._c()
+    s = Spans._c(spans)
     st = _lib.speechkv_pool_hidden(h.data_ptr(), h.stride(0), h.stride(1), h.shape[0], h.shape[1],
                                    h.shape[2], _dtype_code(h.dtype), s, w,
                                    _ptr(gate_u), out.data_ptr(), out.stride(0), out.stride(1),
@@ -342,7 +349,7 @@ def speechkv_decode_attn(q: torch.Tensor, cache: PagedKV, cache_len: torch.Tenso
     B, Hq, D = q.shape
     if scale is None:
         scale = D ** -0.5
-    c = cache._c()
+    c = PagedKV._c(cache)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = _lib.speechkv_decode_attn(q.data_ptr(), B, Hq, c, cache_len.data_ptr(),
                                    max_cache_len, _ptr(k_new), _ptr(v_new), scale, num_splits,
@@ -364,7 +371,7 @@ def speechkv_decode_attn_noalloc(q: torch.Tensor, cache: PagedKV, cache_len: tor
     B, Hq, D = q.shape
     if scale is None:
         scale = D ** -0.5
-    c = cache._c()
+    c = PagedKV._c(cache)
     st = _lib.speechkv_decode_attn_noalloc(q.data_ptr(), B, Hq, c,
                                            cache_len.data_ptr(), max_cache_len, _ptr(k_new),
                                            _ptr(v_new), scale, num_splits, out.data_ptr(),
@@ -383,8 +390,8 @@ def speechkv_prefill_attn(q: torch.Tensor, cache: PagedKV, spans: Spans, w: int,
     B, q_len, Hq, D = q.shape
     if scale is None:
         scale = D ** -0.5
-    c = cache._c()
-    s = spans._c()
+    c = PagedKV._c(cache)
+    s = Spans._c(spans)
     st = _lib.speechkv_prefill_attn(q.data_ptr(), B, Hq, q_len, c, s,
                                     w, layer, l0, mask_mode, scale, out.data_ptr(), _ptr(lse),
                                     _stream(stream))
@@ -411,8 +418,8 @@ def speechkv_pool_prefill_attn(q: torch.Tensor, k_raw: torch.Tensor, v_raw: torc
     if scale is None:
         scale = D ** -0.5
     sb, ss, sh, _ = k_raw.stride()
-    c = cache._c()
-    s = spans._c()
+    c = PagedKV._c(cache)
+    s = Spans._c(spans)
     st = _lib.speechkv_pool_prefill_attn(q.data_ptr(), B, Hq, q_len, k_raw.data_ptr(),
                                          v_raw.data_ptr(), sb, ss, sh, k_raw.shape[1],
                                          s, w, _ptr(gate_u), layer, l0,
@@ -433,7 +440,7 @@ def speechkv_prefill_attn_bwd(q: torch.Tensor, cache: PagedKV, spans: Spans, w: 
     """q, out, dout, dq: [B, q_len, Hq, D]; lse: [B, Hq, q_len] fp32;
     dk_hat, dv_hat: [B, hat_capacity, Hkv, D] fp32; workspace: device bytes."""
     _prefill_attn_bwd(_lib.speechkv_prefill_attn_bwd, "speechkv_prefill_attn_bwd", q, cache,
-                      spans, w, layer, l0, out, lse, dout, dq, dk_hat, dv_hat, workspace,
+                      Spans._c(spans), w, layer, l0, out, lse, dout, dq, dk_hat, dv_hat, workspace,
                       mask_mode, scale, stream)
 
 
@@ -445,11 +452,11 @@ def speechkv_prefill_attn_bwd_segments(q: torch.Tensor, cache: PagedKV, segs: Se
                                        scale: Optional[float] = None, stream=None) -> None:
     """speechkv_prefill_attn_bwd for sequences given as segment tables."""
     _prefill_attn_bwd(_lib.speechkv_prefill_attn_bwd_segments, "speechkv_prefill_attn_bwd_segments",
-                      q, cache, segs, w, layer, l0, out, lse, dout, dq, dk_hat, dv_hat, workspace,
-                      mask_mode, scale, stream)
+                      q, cache, Segments._c(segs), w, layer, l0, out, lse, dout, dq, dk_hat, dv_hat,
+                      workspace, mask_mode, scale, stream)
 
 
-def _prefill_attn_bwd(fn, name, q, cache, spans, w, layer, l0, out, lse, dout, dq, dk_hat, dv_hat,
+def _prefill_attn_bwd(fn, name, q, cache, s, w, layer, l0, out, lse, dout, dq, dk_hat, dv_hat,
                       workspace, mask_mode, scale, stream):
     for x in (q, out, dout, dq, lse, dk_hat, dv_hat, workspace):
         if not x.is_contiguous():
@@ -461,8 +468,7 @@ def _prefill_attn_bwd(fn, name, q, cache, spans, w, layer, l0, out, lse, dout, d
     B, q_len, Hq, D = q.shape
     if scale is None:
         scale = D ** -0.5
-    c = cache._c()
-    s = spans._c()
+    c = PagedKV._c(cache)
     st = fn(q.data_ptr(), B, Hq, q_len, c, s, w, layer, l0, mask_mode,
             scale, out.data_ptr(), lse.data_ptr(), dout.data_ptr(), dq.data_ptr(),
             dk_hat.data_ptr(), dv_hat.data_ptr(), dk_hat.shape[1], workspace.data_ptr(),
@@ -484,8 +490,8 @@ def speechkv_pool_kv_bwd(k_raw: torch.Tensor, v_raw: torch.Tensor, spans: Spans,
     """k_raw, v_raw, dk_raw, dv_raw: [B, S_raw, Hkv, D] with one stride and a
     contiguous last axis; dk_hat, dv_hat: [B, capacity, Hkv, D] fp32; du:
     [Hkv, D] fp32 or None."""
-    _pool_kv_bwd(_lib.speechkv_pool_kv_bwd, "speechkv_pool_kv_bwd", k_raw, v_raw, spans, w, gate_u,
-                 layer, l0, dk_hat, dv_hat, dk_raw, dv_raw, du, workspace, stream)
+    _pool_kv_bwd(_lib.speechkv_pool_kv_bwd, "speechkv_pool_kv_bwd", k_raw, v_raw, Spans._c(spans), w,
+                 gate_u, layer, l0, dk_hat, dv_hat, dk_raw, dv_raw, du, workspace, stream)
 
 
 def speechkv_pool_kv_bwd_segments(k_raw: torch.Tensor, v_raw: torch.Tensor, segs: Segments,
@@ -496,10 +502,11 @@ def speechkv_pool_kv_bwd_segments(k_raw: torch.Tensor, v_raw: torch.Tensor, segs
                                   workspace: Optional[torch.Tensor] = None, stream=None) -> None:
     """speechkv_pool_kv_bwd for sequences given as segment tables."""
     _pool_kv_bwd(_lib.speechkv_pool_kv_bwd_segments, "speechkv_pool_kv_bwd_segments", k_raw, v_raw,
-                 segs, w, gate_u, layer, l0, dk_hat, dv_hat, dk_raw, dv_raw, du, workspace, stream)
+                 Segments._c(segs), w, gate_u, layer, l0, dk_hat, dv_hat, dk_raw, dv_raw, du, workspace,
+                 stream)
 
 
-def _pool_kv_bwd(fn, name, k_raw, v_raw, spans, w, gate_u, layer, l0, dk_hat, dv_hat, dk_raw,
+def _pool_kv_bwd(fn, name, k_raw, v_raw, s, w, gate_u, layer, l0, dk_hat, dv_hat, dk_raw,
                  dv_raw, du, workspace, stream):
     for x in (v_raw, dk_raw, dv_raw):
         if x.shape != k_raw.shape or x.stride() != k_raw.stride() or x.dtype != k_raw.dtype:
@@ -511,7 +518,6 @@ def _pool_kv_bwd(fn, name, k_raw, v_raw, spans, w, gate_u, layer, l0, dk_hat, dv
             raise ValueError("dk_hat, dv_hat and du are contiguous fp32")
     B, S, H, D = k_raw.shape
     sb, ss, sh, _ = k_raw.stride()
-    s = spans._c()
     ws = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = fn(k_raw.data_ptr(), v_raw.data_ptr(), sb, ss, sh, B, S, H, D, _dtype_code(k_raw.dtype),
             s, w, _ptr(gate_u), layer, l0, dk_hat.data_ptr(), dv_hat.data_ptr(),

@@ -603,3 +603,67 @@ def test_valid_calls_pass_every_check():
     assert prefill_bwd() == E_HIP
     assert pool_bwd() == E_HIP
     assert pool_hidden() == E_HIP
+
+
+def descriptions():
+    """A cache, one-run spans and a segment table on the host, for the
+    binding's own checks (nothing is launched on these paths)."""
+    import torch
+    i32 = lambda *n: torch.zeros(*n, dtype=torch.int32)  # noqa: E731
+    pages = torch.zeros(4, 2, 16, 64, dtype=torch.bfloat16)
+    return dict(cache=skv.PagedKV(pages, pages.clone(), i32(1, 4)),
+                spans=skv.Spans(i32(1), i32(1), i32(1), 0, 8),
+                segs=skv.Segments(i32(2), i32(3), i32(3), 3, 8))
+
+
+def binding_calls(d, where, cache):
+    """Every call of the binding that takes a description, with the segment
+    table's object in `where["segs"]` and the one-run spans' in `where["spans"]`."""
+    import torch
+    z = lambda *n, t=torch.bfloat16: torch.zeros(*n, dtype=t)  # noqa: E731
+    raw, q, lse, hat = z(1, 8, 2, 64), z(1, 8, 4, 64), z(1, 4, 8, t=torch.float32), z(1, 8, 2, 64, t=torch.float32)
+    ws, gate = z(4096, t=torch.uint8), None
+    one, seg = where["spans"], where["segs"]
+    bwd = lambda f, w: f(q, cache, w, 4, 1, 0, q.clone(), lse, q.clone(), q.clone(), hat, hat.clone(), ws, stream=0)  # noqa: E731,E501
+    pbwd = lambda f, w: f(raw, raw.clone(), w, 4, gate, 1, 0, hat, hat.clone(), raw.clone(), raw.clone(), stream=0)  # noqa: E731,E501
+    return {
+        "pool_kv": lambda: skv.speechkv_pool_kv(raw, raw, one, 4, gate, 1, 0, cache, stream=0),
+        "pool_kv_segments": lambda: skv.speechkv_pool_kv_segments(raw, raw, seg, 4, gate, 1, 0, cache, stream=0),
+        "prefill_attn": lambda: skv.speechkv_prefill_attn(q, cache, one, 4, 1, 0, q.clone(), stream=0),
+        "prefill_attn_segments": lambda: skv.speechkv_prefill_attn_segments(q, cache, seg, 4, 1, 0, q.clone(), stream=0),
+        "pool_prefill_attn": lambda: skv.speechkv_pool_prefill_attn(q, raw, raw, one, 4, gate, 1, 0, cache, q.clone(), stream=0),
+        "prefill_attn_bwd": lambda: bwd(skv.speechkv_prefill_attn_bwd, one),
+        "prefill_attn_bwd_segments": lambda: bwd(skv.speechkv_prefill_attn_bwd_segments, seg),
+        "pool_kv_bwd": lambda: pbwd(skv.speechkv_pool_kv_bwd, one),
+        "pool_kv_bwd_segments": lambda: pbwd(skv.speechkv_pool_kv_bwd_segments, seg),
+        "pool_hidden": lambda: skv.speechkv_pool_hidden(z(1, 8, 128), one, 4, gate, z(1, 8, 128), stream=0),
+        "decode_attn": lambda: skv.speechkv_decode_attn(q[:, 0].contiguous(), cache, z(1, t=torch.int32), 8,
+                                                        q[:, 1].contiguous(), stream=0),
+        "decode_attn_noalloc": lambda: skv.speechkv_decode_attn_noalloc(
+            q[:, 0].contiguous(), cache, z(1, t=torch.int32), 8, q[:, 1].contiguous(), stream=0),
+    }
+
+
+ONE_RUN_CALLS = ("pool_kv", "prefill_attn", "pool_prefill_attn", "prefill_attn_bwd", "pool_kv_bwd", "pool_hidden")
+SEGMENT_CALLS = ("pool_kv_segments", "prefill_attn_segments", "prefill_attn_bwd_segments", "pool_kv_bwd_segments")
+CACHE_CALLS = ("pool_kv", "pool_kv_segments", "prefill_attn", "prefill_attn_segments", "pool_prefill_attn",
+               "prefill_attn_bwd", "prefill_attn_bwd_segments", "decode_attn", "decode_attn_noalloc")
+
+
+@pytest.mark.parametrize("call,given", [(c, g) for c in ONE_RUN_CALLS for g in ("segs", "cache")] +
+                         [(c, g) for c in SEGMENT_CALLS for g in ("spans", "cache")])
+def test_binding_refuses_the_other_kind_of_span_description(call, given):
+    """The descriptions have different layouts: one taken for another would
+    have the library read lengths where it expects pointers."""
+    d = descriptions()
+    calls = binding_calls(d, dict(spans=d[given], segs=d[given]), d["cache"])
+    with pytest.raises(TypeError):
+        calls[call]()
+
+
+@pytest.mark.parametrize("call", CACHE_CALLS)
+@pytest.mark.parametrize("given", ["spans", "segs"])
+def test_binding_refuses_spans_for_a_cache(call, given):
+    d = descriptions()
+    with pytest.raises(TypeError):
+        binding_calls(d, d, d[given])[call]()
