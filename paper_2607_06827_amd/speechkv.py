@@ -67,9 +67,7 @@ class _Segments(ctypes.Structure):
 # of them for any other, so each _c below checks the type of its object.
 _pack_paged_kv = struct.Struct("@PPPiiiiii").pack
 _pack_spans = struct.Struct("@PPPii").pack
-_pack_segments = struct.Struct("@PPPiii").pack
-assert struct.calcsize("@PPPiiiiii") == ctypes.sizeof(_PagedKV)
-assert struct.calcsize("@PPPii") == ctypes.sizeof(_Spans)
+_pack_segments = struct.Struct("@PPPiii4x").pack  # (padded to the structure's 8-byte alignment)
 
 _vp, _i32, _i64, _f32, _sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
 _lib.speechkv_pool_kv.argtypes = [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp,

@@ -667,3 +667,24 @@ def test_binding_refuses_spans_for_a_cache(call, given):
     d = descriptions()
     with pytest.raises(TypeError):
         binding_calls(d, d, d[given])[call]()
+
+
+@pytest.mark.parametrize("name,struct", [("cache", skv._PagedKV), ("spans", skv._Spans), ("segs", skv._Segments)])
+def test_packed_descriptions_fill_their_c_structures(name, struct):
+    """The bytes the library is handed are as long as the structure it reads,
+    and read back field by field as what the object holds."""
+    x = descriptions()[name]
+    packed = x._c()
+    assert len(packed) == ctypes.sizeof(struct)
+    c = struct.from_buffer_copy(packed)
+    if name == "cache":
+        want = dict(k_pages=x.k_pages.data_ptr(), v_pages=x.v_pages.data_ptr(),
+                    block_table=x.block_table.data_ptr(), num_pages=4, page_size=16, max_pages_per_seq=4,
+                    num_kv_heads=2, head_dim=64, dtype=skv.DTYPE_BF16)
+    elif name == "spans":
+        want = dict(prefix_len=x.prefix_len.data_ptr(), speech_len=x.speech_len.data_ptr(),
+                    suffix_len=x.suffix_len.data_ptr(), max_speech_len=0, max_total_len=8)
+    else:
+        want = dict(seg_start=x.seg_start.data_ptr(), text_len=x.text_len.data_ptr(),
+                    speech_len=x.speech_len.data_ptr(), num_segments=3, max_segments=3, max_total_len=8)
+    assert {f: getattr(c, f) for f, _ in struct._fields_} == want
