@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import dataclasses
+import operator
 import os
 import struct
 from typing import Optional
@@ -68,6 +69,13 @@ class _Segments(ctypes.Structure):
 _pack_paged_kv = struct.Struct("@PPPiiiiii").pack
 _pack_spans = struct.Struct("@PPPii").pack
 _pack_segments = struct.Struct("@PPPiii4x").pack  # (padded to the structure's 8-byte alignment)
+
+
+def _int32s(*counts):
+    """The counts of a description, those outside int32 as -1, which the
+    library refuses (a ctypes field would keep their low 32 bits)."""
+    return (n if -2**31 <= operator.index(n) < 2**31 else -1 for n in counts)
+
 
 _vp, _i32, _i64, _f32, _sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
 _lib.speechkv_pool_kv.argtypes = [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp,
@@ -167,8 +175,12 @@ class PagedKV:
         if t.dtype != torch.int32 or t.dim() != 2:
             raise ValueError("block_table must be int32 [batch, max_pages]")
         pages, heads, page, dim = shape
-        return _pack_paged_kv(k.data_ptr(), v.data_ptr(), t.data_ptr(), pages, page, t.shape[1],
-                              heads, dim, _dtype_code(dtype))
+        try:
+            return _pack_paged_kv(k.data_ptr(), v.data_ptr(), t.data_ptr(), pages, page, t.shape[1],
+                                  heads, dim, _dtype_code(dtype))
+        except struct.error:
+            return _pack_paged_kv(k.data_ptr(), v.data_ptr(), t.data_ptr(),
+                                  *_int32s(pages, page, t.shape[1], heads, dim), _dtype_code(dtype))
 
 
 @dataclasses.dataclass
@@ -188,8 +200,11 @@ class Spans:
         for x in (self.prefix_len, self.speech_len, self.suffix_len):
             if x.dtype != torch.int32 or not x.is_contiguous():
                 raise ValueError("span lengths must be contiguous int32 tensors")
-        return _pack_spans(self.prefix_len.data_ptr(), self.speech_len.data_ptr(),
-                      self.suffix_len.data_ptr(), self.max_speech_len, self.max_total_len)
+        p, t, n = self.prefix_len.data_ptr(), self.speech_len.data_ptr(), self.suffix_len.data_ptr()
+        try:
+            return _pack_spans(p, t, n, self.max_speech_len, self.max_total_len)
+        except struct.error:
+            return _pack_spans(p, t, n, *_int32s(self.max_speech_len, self.max_total_len))
 
 
 @dataclasses.dataclass
@@ -213,9 +228,12 @@ class Segments:
                 raise ValueError("segment tables must be contiguous int32 tensors")
         if self.text_len.shape != self.speech_len.shape:
             raise ValueError("text_len and speech_len must have one entry per segment")
-        return _pack_segments(self.seg_start.data_ptr(), self.text_len.data_ptr(),
-                              self.speech_len.data_ptr(), self.text_len.numel(), self.max_segments,
-                              self.max_total_len)
+        p, t, n = self.seg_start.data_ptr(), self.text_len.data_ptr(), self.speech_len.data_ptr()
+        num = self.text_len.numel()
+        try:
+            return _pack_segments(p, t, n, num, self.max_segments, self.max_total_len)
+        except struct.error:
+            return _pack_segments(p, t, n, *_int32s(num, self.max_segments, self.max_total_len))
 
     @staticmethod
     def from_lists(segs, device="cuda") -> "Segments":

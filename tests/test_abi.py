@@ -688,3 +688,23 @@ def test_packed_descriptions_fill_their_c_structures(name, struct):
         want = dict(seg_start=x.seg_start.data_ptr(), text_len=x.text_len.data_ptr(),
                     speech_len=x.speech_len.data_ptr(), num_segments=3, max_segments=3, max_total_len=8)
     assert {f: getattr(c, f) for f, _ in struct._fields_} == want
+
+
+@pytest.mark.parametrize("bound", [2**31, 2**32 + 8, -1, -2**31 - 1, -2**32 + 8])
+@pytest.mark.parametrize("call", ONE_RUN_CALLS + SEGMENT_CALLS)
+def test_binding_refuses_bounds_the_library_cannot_hold(call, bound):
+    """A row bound outside int32 is the library's invalid argument, whatever
+    its low 32 bits are (8 here is a valid bound)."""
+    d = descriptions()
+    d["spans"].max_total_len = d["segs"].max_total_len = bound
+    with pytest.raises(skv.SpeechKVError) as e:
+        binding_calls(d, d, d["cache"])[call]()
+    assert e.value.status == skv.ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("call", ONE_RUN_CALLS + SEGMENT_CALLS)
+def test_binding_takes_integers_only_as_bounds(call):
+    d = descriptions()
+    d["spans"].max_total_len = d["segs"].max_total_len = 8.0
+    with pytest.raises(TypeError):
+        binding_calls(d, d, d["cache"])[call]()
