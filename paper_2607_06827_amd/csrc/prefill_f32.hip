@@ -172,7 +172,14 @@ __global__ __launch_bounds__(64 * kWaves, waves_per_simd<D>()) void prefill_f32_
     wait_all();  // the last tile's reads
     load_tile<D>(a, w, kt, t, lane);
     wait_all();
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    // values of keys past the visible range (copies of the last one's) are
+    // zero: an infinite one would meet its zero weight as 0 * infinity
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    if (kt == ntiles - 1) {
+      for (int i = (w.kmax - kt * kKeys) * (D / 4) + lane; i < kKeys * (D / 4); i += 64)
+        *reinterpret_cast<f32x4*>(t.v + 4 * i) = zero;
+    }
+    f32x4 s = zero;
 #pragma unroll
     for (int c = 0; c < kDB; ++c) {
       const f32x4 ka = row_read<D>(t.k, j, 4 * c + gq);

@@ -8,7 +8,8 @@ Sizes span several tiles and a ragged tail while the oracle stays fast.
 import pytest
 import torch
 
-from gpu_case import Case, run_and_check
+from gpu_case import Case, build, run_and_check
+from paper_2607_06827_amd import speechkv as skv
 
 pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
@@ -77,3 +78,22 @@ F32_CASES = {
 def test_f32_prefill_kernels_match_oracle(name):
     print(f"case {name}", flush=True)
     run_and_check(F32_CASES[name])
+
+
+@pytest.mark.parametrize("Hkv,D", [(1, 64), (1, 128), (520, 64), (260, 128)])
+def test_f32_prefill_keeps_an_infinite_value_infinite(Hkv, D):
+    """Rows that see an infinite value with a positive weight are infinite,
+    not NaN: the unused keys of a tile must not meet their zero weight as 0 *
+    infinity.  Key 4 is the last visible one of rows 4..44 (the window closes
+    at row 44); few KV heads take the kernel of 16-row blocks, many the one of
+    shared tiles."""
+    case = Case(P=[5], T=[41], N=[0], w=64, Hq=Hkv, Hkv=Hkv, D=D, dtype="f32", decode_steps=1)
+    x = build(case)
+    x["v_raw"][:, 4] = float("inf")
+    t, dev = x["t"], x["dev"]
+    skv.speechkv_pool_kv(t(x["k_raw"]), t(x["v_raw"]), x["spans"], case.w, t(x["u"]), case.layer, case.l0,
+                         x["cache"])
+    out = torch.full((1, x["S"], Hkv, D), float("nan"), device=dev)
+    skv.speechkv_prefill_attn(t(x["q"]), x["cache"], x["spans"], case.w, case.layer, case.l0, out)
+    torch.cuda.synchronize()
+    assert torch.isposinf(out[0, 4:45]).all()
