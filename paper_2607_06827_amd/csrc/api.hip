@@ -25,7 +25,6 @@ static __device__ __align__(256) unsigned char scratch[SPEECHKV_NOALLOC_SCRATCH_
 namespace {
 
 constexpr int kMaxGrid = 65535;
-constexpr int kMaxFusedPairs = 128;  // (sequence, KV head) pairs of the one-kernel pool + prefill
 constexpr int kMaxRows = 2147483647 - SPEECHKV_MAX_WINDOW;  // ceil(T / w) stays in int32
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -104,6 +103,44 @@ int group_of(int num_q_heads, int num_kv_heads) {
   if (num_q_heads < 1 || num_q_heads % num_kv_heads) return -1;
   const int g = num_q_heads / num_kv_heads;
   return (g == 1 || g == 2 || g == 4 || g == 8) ? g : -1;
+}
+
+// Whether speechkv_pool_prefill_attn runs as one kernel that pools each key
+// tile it reads, or as two, the pooling and then the attention over the cache.
+// One kernel saves a launch (calls through the binding in a row are bound by
+// its host path, at 8.5 to 8.7 us with one launch and 10.7 to 12.2 us with two)
+// and, where pooling is a copy, a read of the cache; but its blocks take their key tiles one after
+// the other, each pooled between the products, and pool them once per block of
+// 256 / group rows.  So it takes short calls whose blocks fit the chip at once
+// (one block a CU), measured at 2 to 512 pairs, groups 1 to 8 and 8 to 512 rows.
+// In us of GPU time, one / two:
+//  - more than 128 (sequence, KV head) pairs: two (512 pairs of 64 rows, 64-wide,
+//    w = 4: 11.5 / 9.7), and more than two blocks a pair: two (8 sequences of
+//    1596 rows, 128-wide: 106 / 53);
+//  - 64-wide heads, pooled: one up to two key tiles (w = 4, 16 pairs: 64 rows
+//    5.8 / 7.3, 128 rows 8.0 / 7.9 but 8.7 / 12.1 through the binding, 256 rows
+//    10.5 / 8.5); copied: up to six (64 rows 6.1 / 7.3, 128 rows 8.7 / 8.6, 256
+//    rows 13.6 / 10.9);
+//  - 128-wide heads, whose tile costs twice as much: one only where the attention
+//    alone would have one block a pair too (groups 1, 2, 4, 16 pairs, copied: 128
+//    rows 11.6 / 9.8 and 11.9 / 12.3 through the binding, 64 rows 8.9 / 8.4, 32
+//    rows 7.6 / 7.6; one size up 19.5 / 12.9, 14.2 / 9.9, 11.3 / 8.3) or the group
+//    is 8 (64 rows 11.6 / 12.3), and pooled only up to one key tile (group 2, w =
+//    4: 64 rows 8.4 / 8.2, 128 rows 13.4 / 9.0);
+//  - copies of 96 pairs or more: one (128 pairs of 512 rows, 128-wide: 36.5 /
+//    47.4; 64 pairs 33.3 / 31.4), as reading the cache back costs more than the
+//    chain.
+// (max_total_len - max_speech_len + ceil(max_speech_len / w) estimates the keys
+// of the longest sequence.)
+bool pool_prefill_one_kernel(int head_dim, int group, int64_t pairs, int w_eff, const speechkv_spans* s) {
+  const int rows = s->max_total_len, block_rows = skv::prefill_fused_rows_per_tile(group);
+  if (pairs > 128 || rows > 2 * block_rows) return false;
+  if (w_eff == 1 && pairs >= 96) return true;
+  const int keys = rows - s->max_speech_len + (s->max_speech_len + w_eff - 1) / w_eff;
+  const int key_tiles = (keys + 31) / 32;
+  if (head_dim == 64) return key_tiles <= (w_eff == 1 ? 6 : 2);
+  const bool one_row_tile = group == 8 || rows <= skv::prefill_rows_per_tile(SPEECHKV_DTYPE_BF16, group);
+  return one_row_tile && (w_eff == 1 || key_tiles <= 1);
 }
 
 int64_t page_pool_bytes(const speechkv_paged_kv* c) {
@@ -620,15 +657,11 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
     for (int j = i + 1; j < 4; ++j)
       if (wr[j] && overlaps(wr[i], wr_n[i], wr[j], wr_n[j])) return SPEECHKV_ERR_ALIAS;
   }
-  // Below l0 pooling is a copy: where at most two blocks of 256 / group rows
-  // read a key tile, and the blocks fit the chip at once, one kernel that
-  // copies its tiles on the fly saves a launch (31 sequences of 165 rows, 8/4
-  // heads of 64: 12.0 us against 13.5; 64 sequences, 16/8 heads of 128: 66.5 us
-  // against 46.5).
-  const int fused_rows = skv::prefill_fused_rows_per_tile(group);
-  int64_t fused_tiles = (spans->max_total_len + fused_rows - 1) / fused_rows;
-  if (fused_tiles < 1) fused_tiles = 1;  // (tile 0 writes cache_len_out)
-  if ((layer < l0 || w == 1) && fused_tiles <= 2 && (int64_t)batch * cache->num_kv_heads <= kMaxFusedPairs) {
+  const int w_eff = layer >= l0 ? w : 1;
+  if (pool_prefill_one_kernel(D, group, (int64_t)batch * cache->num_kv_heads, w_eff, spans)) {
+    const int fused_rows = skv::prefill_fused_rows_per_tile(group);
+    // at least one tile per (sequence, head): tile 0 writes cache_len_out
+    const int fused_tiles = std::max(1, (spans->max_total_len + fused_rows - 1) / fused_rows);
     skv::PrefillFusedArgs f;
     skv::PrefillArgs& a = f.at;
     a.q = q;
@@ -641,11 +674,11 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
     a.prefix_len = spans->prefix_len;
     a.speech_len = spans->speech_len;
     a.suffix_len = spans->suffix_len;
-    a.w_eff = layer >= l0 ? w : 1;
+    a.w_eff = w_eff;
     a.mask_mode = mask_mode;
     a.q_len = q_len;
     a.q_rows = spans->max_total_len;
-    a.num_tiles = (int)fused_tiles;
+    a.num_tiles = fused_tiles;
     a.num_q_heads = num_q_heads;
     a.scale_log2 = scale * 1.4426950408889634f;
     f.k_pages = cache->k_pages;
@@ -667,10 +700,7 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
   const int64_t slots = (int64_t)cache->max_pages_per_seq * cache->page_size;
   const int max_out = spans->max_total_len < slots ? spans->max_total_len : (int)slots;
   if (skv::pool_grid_blocks(max_out, cache->num_kv_heads, D) > INT32_MAX) return SPEECHKV_ERR_INVALID_ARG;
-  // Pool into the cache, then attend over it: pooling inside the attention
-  // would pool every key tile again for each query block that sees it (1596 x
-  // 471, b = 8: 106 us in one kernel, 14 + 39 us in two; one sequence of 298 x
-  // 53 rows: 14.9 us in one, 11 us in two).
+  // pool into the cache, then attend over it
   skv::PoolArgs pa;
   pa.k_raw = k_raw;
   pa.v_raw = v_raw;
@@ -681,7 +711,7 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
   pa.prefix_len = spans->prefix_len;
   pa.speech_len = spans->speech_len;
   pa.suffix_len = spans->suffix_len;
-  pa.w_eff = layer >= l0 ? w : 1;
+  pa.w_eff = w_eff;
   pa.gate = gate_u;
   pa.k_pages = cache->k_pages;
   pa.v_pages = cache->v_pages;
@@ -704,7 +734,7 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
   a.prefix_len = spans->prefix_len;
   a.speech_len = spans->speech_len;
   a.suffix_len = spans->suffix_len;
-  a.w_eff = pa.w_eff;
+  a.w_eff = w_eff;
   a.mask_mode = mask_mode;
   a.q_len = q_len;
   a.q_rows = spans->max_total_len;

@@ -6,6 +6,7 @@ and LSE, and every decode output with the oracle.  Test infrastructure only.
 """
 from __future__ import annotations
 
+import ctypes
 import dataclasses
 import math
 from typing import List, Optional
@@ -73,6 +74,32 @@ def guarded(shape, dtype, dev, fill=float("nan")):
         assert bool(torch.all(raw[GUARD + n * esz:] == GUARD_BYTE)), f"{what}: guard after it overwritten"
 
     return t, check
+
+
+class _KernelNode(ctypes.Structure):  # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("shared", ctypes.c_uint)]
+
+
+def launches(fn):
+    """(blocks, threads per block) of the kernels fn() launches, in order, from
+    a captured graph that is not run: which kernels a call dispatches to."""
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        fn()
+    hip = skv._lib  # (its HIP runtime)
+    n = ctypes.c_size_t(0)
+    raw = ctypes.c_void_p(g.raw_cuda_graph())
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        kind, k = ctypes.c_int(-1), _KernelNode()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0 and kind.value == 0
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(k)) == 0
+        out.append((k.grid[0] * k.grid[1] * k.grid[2], k.block[0] * k.block[1] * k.block[2]))
+    return out
 
 
 def build(case: Case, device="cuda"):

@@ -1,19 +1,21 @@
-"""GPU parity of the one-launch pooling + prefill attention
-(speechkv_pool_prefill_attn, the on-the-fly pooling of Sec. III-C).
+"""GPU parity of the pooling + prefill attention in one call
+(speechkv_pool_prefill_attn, the pooling inside the forward pass of Sec. III-C).
 
 It must leave exactly what speechkv_pool_kv followed by speechkv_prefill_attn
 leave: the cache rows, the cache lengths, the outputs and the LSE, bit for
 bit (the pooled rows come from the same arithmetic).  It is also compared
 with the fp64 oracle directly, on small and adversarial shapes (windows
 longer than four frames, ragged windows, empty spans, every group size, both
-head sizes and masks, strided raw views) and on full-size workloads.
+head sizes and masks, strided raw views) and on full-size workloads.  Short
+calls are one kernel that pools each key tile on the fly, the others two: the
+cases of ONE and TWO check which.
 """
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from gpu_case import Case, build
+from gpu_case import Case, build, launches
 from helpers import TOL, f64, fwd_err, gather
 from paper_2607_06827_amd import inputs
 from paper_2607_06827_amd import speechkv as skv
@@ -139,6 +141,65 @@ def test_fused_equals_split_and_oracle(name):
     x, res = run_both(case)
     check_same(case, x, res)
     check_oracle(case, x, res)
+
+
+# Calls of one kernel, at the edges of its rows (256 / G a block, two blocks at
+# most) and of the sizes it is dispatched for: every group and head size, pooled
+# and copied.  Short sequences before and after the longest leave rows of the
+# last block, and whole blocks, empty.
+def _around(n, w, text=3, **kw):
+    """Sequences of n rows, of one row, of none, and of half."""
+    return Case(P=[text, 1, 0, n // 4], T=[n - text, 0, 0, n // 4], N=[0, 0, 0, n // 2 - n // 4], w=w, **kw)
+
+
+ONE = {}
+for G, rows in ((1, 128), (2, 64), (4, 32), (8, 32)):
+    heads = dict(Hq=2 * G, Hkv=2)
+    # 128-wide heads: up to one row tile of the attention (group 8: two blocks)
+    ONE[f"d128-g{G}-pooled"] = _around(rows, 16 if G == 1 else 4, D=128, **heads)
+    ONE[f"d128-g{G}-copied"] = _around(rows, 1, text=rows // 3, D=128, page_size=8, **heads)
+    # 64-wide heads: up to two key tiles pooled, six copied
+    ONE[f"d64-g{G}-pooled"] = _around(min(2 * 256 // G, 64 * 2), 4, D=64, page_size=64, **heads)
+    ONE[f"d64-g{G}-copied"] = _around(min(2 * 256 // G, 192), 4, layer=2, l0=5, D=64, **heads)
+    ONE[f"d64-g{G}-one-block"] = _around(min(256 // G, 128) - 1, 6, D=64, mode=1, **heads)
+ONE["d128-g8-two-blocks"] = _around(64, 4, D=128, Hq=16, Hkv=2, mode=1)
+ONE["d64-g8-33-rows"] = _around(33, 3, D=64, Hq=16, Hkv=2, page_size=8)
+ONE["d64-w65536"] = _around(128, 65536, D=64, Hq=4, Hkv=2, zero_gate=True)
+ONE["d128-96-pairs-two-blocks"] = Case(P=[1] * 45 + [40, 2, 0], T=[i % 9 for i in range(45)] + [216, 253, 0],
+                                       N=[i % 3 for i in range(45)] + [0, 0, 0], w=1, D=128, Hq=4, Hkv=2)
+ONE["d64-128-pairs-g1-two-blocks"] = Case(P=[0] * 63 + [12], T=[i % 7 for i in range(63)] + [500], N=[0] * 64,
+                                          layer=0, l0=1, D=64, Hq=2, Hkv=2)
+# ... and the next size up, of two kernels
+TWO = {
+    "d64-pooled-three-key-tiles": Case(P=[65], T=[0], N=[0], D=64, Hq=4, Hkv=2),
+    "d64-copied-seven-key-tiles": Case(P=[3], T=[190], N=[0], w=1, D=64, Hq=2, Hkv=2),
+    "d64-129-pairs": Case(P=[2] * 129, T=[9] * 129, N=[0] * 129, D=64, Hq=1, Hkv=1),
+    "d64-copied-129-pairs": Case(P=[2] * 129, T=[9] * 129, N=[0] * 129, w=1, D=64, Hq=1, Hkv=1),
+    "d64-g8-three-blocks": Case(P=[5], T=[60], N=[0], D=64, Hq=8, Hkv=1),
+    "d128-pooled-two-key-tiles": Case(P=[33], T=[0], N=[0], D=128, Hq=4, Hkv=2),
+    "d128-g1-two-row-tiles": Case(P=[3], T=[126], N=[0], w=1, D=128, Hq=2, Hkv=2),
+    "d128-g2-two-row-tiles": Case(P=[3], T=[62], N=[0], w=8, D=128, Hq=4, Hkv=2),
+    "d128-g4-two-row-tiles": Case(P=[3], T=[30], N=[0], w=8, D=128, Hq=8, Hkv=2),
+    "d128-95-pairs-two-blocks": Case(P=[1] * 94 + [40], T=[i % 9 for i in range(94)] + [216], N=[0] * 95, w=1,
+                                     D=128, Hq=2, Hkv=1),
+    "d128-96-pairs-three-blocks": Case(P=[1] * 95 + [40], T=[i % 9 for i in range(95)] + [217], N=[0] * 96, w=1,
+                                       D=128, Hq=2, Hkv=1),
+}
+
+
+@pytest.mark.parametrize("name", sorted(ONE) + sorted(TWO))
+def test_one_kernel_and_two_at_their_edges(name):
+    case = ONE.get(name) or TWO[name]
+    print(f"case {name}", flush=True)
+    x, res = run_both(case, raw_view=name in ("d128-g2-pooled", "d64-g4-copied"))
+    check_same(case, x, res)
+    check_oracle(case, x, res)
+    t = x["t"]
+    q, k, v, u = t(x["q"]), t(x["k_raw"]), t(x["v_raw"]), t(x["u"])
+    out = torch.empty_like(q)
+    run = launches(lambda: skv.speechkv_pool_prefill_attn(q, k, v, x["spans"], case.w, u, case.layer, case.l0,
+                                                          x["cache"], out, mask_mode=case.mode))
+    assert len(run) == (1 if name in ONE else 2), run
 
 
 def test_fused_strided_raw_views():
