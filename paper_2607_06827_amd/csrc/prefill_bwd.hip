@@ -519,8 +519,8 @@ __global__ __launch_bounds__(DqShape16<G>::kThreads, 3) void prefill_bwd_dq16_ke
   delta0 += __shfl_xor(delta0, 32, 64);
   const float lse2 = lse * kLog2eF;
 
-  // fragment addresses (bytes), one register per tile and pattern, as in the
-  // dK/dV kernel: row-wise operands of S^T / dP^T at ar ^ 64c (+16 rows for
+  // fragment addresses (bytes), one register per tile and pattern (patterns as
+  // in the dK/dV kernel): row-wise operands of S^T / dP^T at ar ^ 64c (+16 rows for
   // the second key block), transposed K^T operands at at ^ 32db (+16 rows)
   const int rr = 4 * gq + (j >> 2);
   const uint32_t ar_off = (uint32_t)(j * D * 2 + ((gq ^ Q::swz(j)) << 4));
@@ -814,32 +814,39 @@ __global__ __launch_bounds__(64 * kWaves * SG, SG == 1 ? 3 : kWaves * SG / 4) vo
 #pragma unroll
     for (int i = 0; i < 4; ++i) dk[db][i] = dv[db][i] = 0.f;
 
-  // Fragment addresses (bytes), one register per tile and pattern:
+  // Fragment addresses (bytes) in the Q tile of the group's first buffer, one
+  // register per pattern; the other buffers, and the dO tiles, are a multiple of
+  // 256 bytes further, in the reads' immediate offsets (that leaves the bits
+  // of the XORs alone).  With a register per pattern, tile and buffer the third
+  // buffer's spilled, and reloading them waited for the direct loads in flight.
   //  - row-wise A operand of S / dP: lane (gq, j) reads row 16blk + j, chunk
   //    (4c + gq) ^ swz(row) = 4c ^ x with x = gq ^ swz(j) (swz(16blk + j) =
-  //    swz(j)): address ar ^ 64c, plus 16 rows for blk = 1;
+  //    swz(j)): address ar0 ^ 64c, plus 16 rows for blk = 1;
   //  - transposed A operand of dV^T / dK^T (ds_read_b64_tr_b16): lane j of
   //    group gq points at row 4gq + j/4 (and 16 + 4gq + j/4), elements 16db +
   //    4(j%4) .. +3, i.e. chunk 2db + e (e = (j%4)/2) at position 2db ^ (e ^
-  //    swz(row)), swz(row) the same for both rows: address at ^ 32db.
+  //    swz(row)), swz(row) the same for both rows: address at0 ^ 32db.
   const int rr = 4 * gq + (j >> 2);
-  const uint32_t ar_off = (uint32_t)(j * D * 2 + ((gq ^ Q::swz(j)) << 4));
-  const uint32_t at_off = (uint32_t)(rr * D * 2 + ((((j & 3) >> 1) ^ Q::swz(rr)) << 4) + ((j & 1) << 3));
+  const uint32_t tile0 = lds_addr(s_buf[sg][0].q);
+  const uint32_t ar0 = tile0 + (uint32_t)(j * D * 2 + ((gq ^ Q::swz(j)) << 4));
+  const uint32_t at0 = tile0 + (uint32_t)(rr * D * 2 + ((((j & 3) >> 1) ^ Q::swz(rr)) << 4) + ((j & 1) << 3));
   const float neg_inv_scale = -1.f / a.scale;
   typedef __attribute__((address_space(3))) const u16x8_t* lds_frag_ptr;
 
-  // step n from buffer bf; the loads of steps n+1 and n+2 may be in flight
-  auto compute = [&](int n, const Buf& bf) __attribute__((always_inline)) {
+  // step n from buffer par; the loads of the next kBufs - 1 steps may be in flight
+  auto compute = [&](int n, auto par) __attribute__((always_inline)) {
+    const Buf& bf = s_buf[sg][decltype(par)::value];
+    constexpr uint32_t kTileQ = decltype(par)::value * sizeof(Buf), kTileG = kTileQ + Q::kElems * sizeof(T);
+    static_assert(sizeof(Buf) % 256 == 0 && Q::kElems * sizeof(T) % 256 == 0, "tiles on 256-byte boundaries");
     const int q0 = (t1 - 1 - ((n * SG + sg) >> gshift)) * kQ;
     if (q0 + kQ <= wave_from) return;  // no row of the tile sees a key of this wave
-    uint32_t ar_q = lds_addr(bf.q) + ar_off, ar_g = lds_addr(bf.g) + ar_off;
-    uint32_t at_q = lds_addr(bf.q) + at_off, at_g = lds_addr(bf.g) + at_off;
-    asm volatile("" : "+v"(ar_q), "+v"(ar_g), "+v"(at_q), "+v"(at_g));
-    auto arow = [&](uint32_t base, int blk, int c) __attribute__((always_inline)) {
-      return __builtin_bit_cast(Frag, *(lds_frag_ptr)(uintptr_t)((base ^ (uint32_t)(64 * c)) + (uint32_t)(blk * 16 * D * 2)));
+    uint32_t ar = ar0, at = at0;
+    asm volatile("" : "+v"(ar), "+v"(at));  // (keeps the XORed addresses from being held across steps)
+    auto arow = [&](uint32_t tile, int blk, int c) __attribute__((always_inline)) {
+      return __builtin_bit_cast(Frag, *(lds_frag_ptr)(uintptr_t)((ar ^ (uint32_t)(64 * c)) + (tile + (uint32_t)(blk * 16 * D * 2))));
     };
-    auto atr = [&](uint32_t base, int db) __attribute__((always_inline)) {
-      const uint32_t al = base ^ (uint32_t)(32 * db);
+    auto atr = [&](uint32_t tile, int db) __attribute__((always_inline)) {
+      const uint32_t al = (at ^ (uint32_t)(32 * db)) + tile;
       const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)al);
       const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(al + 16 * D * 2));
       const u16x8_t v = {(unsigned short)lo[0], (unsigned short)lo[1], (unsigned short)lo[2], (unsigned short)lo[3],
@@ -862,7 +869,7 @@ __global__ __launch_bounds__(64 * kWaves * SG, SG == 1 ? 3 : kWaves * SG / 4) vo
     constexpr int kNS = 4 * kDC;  // (c, blk, S or dP)
     auto aop = [&](int idx) __attribute__((always_inline)) {
       const int c = idx / 4, blk = (idx / 2) % 2, t = idx % 2;
-      return arow(t ? ar_g : ar_q, blk, c);
+      return arow(t ? kTileG : kTileQ, blk, c);
     };
     constexpr int kAheadS = 4;
     Frag sb[kAheadS];
@@ -886,7 +893,7 @@ __global__ __launch_bounds__(64 * kWaves * SG, SG == 1 ? 3 : kWaves * SG / 4) vo
 
     // the first transposed operands of dV / dK, read during the softmax
     constexpr int kNT = 2 * kDB;  // (db, dV or dK)
-    auto top = [&](int idx) __attribute__((always_inline)) { return atr(idx % 2 ? at_q : at_g, idx / 2); };
+    auto top = [&](int idx) __attribute__((always_inline)) { return atr(idx % 2 ? kTileQ : kTileG, idx / 2); };
     constexpr int kAheadT = 4;
     Frag tb[kAheadT];
 #pragma unroll
@@ -945,7 +952,7 @@ __global__ __launch_bounds__(64 * kWaves * SG, SG == 1 ? 3 : kWaves * SG / 4) vo
     constexpr int kPar = decltype(par)::value;
     // (into the buffer step n-1 used)
     if (n + kBufs - 1 < n_steps) load_step(n + kBufs - 1, s_buf[sg][(kPar + kBufs - 1) % kBufs]);
-    if (SG == 1 || n < n_steps) compute(n, s_buf[sg][kPar]);
+    if (SG == 1 || n < n_steps) compute(n, par);
     barrier_after(n);
   };
   for (int n = 0; n < max_steps; n += kBufs) {
