@@ -782,17 +782,11 @@ __global__ __launch_bounds__(64 * kWaves * SG, SG == 1 ? 3 : kWaves * SG / 4) vo
     }
   };
 
-  // prologue: steps 0 and 1 and this wave's K and V operands, in flight
-  // together and waited for together (the K/V loads are the compiler's: it
-  // may move or spill their registers)
-  const int my_vm = kVm + (wave == kWaves - 1 ? 1 : 0);
-  if (n_steps > 0) load_step(0, s_buf[sg][0]);
-  if (kBufs > 2 && n_steps > 1) load_step(1, s_buf[sg][1]);
   // K and V operands of this lane's key: elements 32c + 8 gq .. +7 (B operand
   // layout of S = Q K^T and dP = dO V^T); a key past the cache or without a
   // page reads a row of page 0 (its column of every product is never stored)
   Frag kf[kDC], vf[kDC];
-  {
+  auto load_kv = [&]() __attribute__((always_inline)) {
     const int shift = a.pv.page_shift;
     const int32_t e = a.table[(int64_t)b * a.pv.max_pages + min(key >> shift, a.pv.max_pages - 1)];
     const bool ok = key < clen && e >= 0 && e < a.pv.num_pages;
@@ -804,7 +798,20 @@ __global__ __launch_bounds__(64 * kWaves * SG, SG == 1 ? 3 : kWaves * SG / 4) vo
       kf[c] = Mfma<T>::load(kp + 32 * c);
       vf[c] = Mfma<T>::load(vp + 32 * c);
     }
-  }
+  };
+  // prologue: the first kBufs - 1 steps and the K and V operands, in flight
+  // together and waited for together (the K/V loads are the compiler's: it may
+  // move or spill their registers).  The operands first, but for d = 64 with
+  // more than a block a CU (us of the attention backward, operands behind /
+  // before the steps: d = 128, 92 x 47, b = 64 39.7 / 38.9, 407 x 126, b = 64,
+  // 32/8 heads 331 / 313; d = 64, 92 x 47, b = 1 13.8 / 13.6 and b = 16 15.4 /
+  // 15.0, but 92 x 62, b = 64 26.5 / 26.7, 782 x 220, b = 32 97 / 99).
+  const int my_vm = kVm + (wave == kWaves - 1 ? 1 : 0);
+  const bool kv_first = D == 128 || gridDim.x <= kCus;
+  if (kv_first) load_kv();
+  if (n_steps > 0) load_step(0, s_buf[sg][0]);
+  if (kBufs > 2 && n_steps > 1) load_step(1, s_buf[sg][1]);
+  if (!kv_first) load_kv();
   bare_barrier<0>();
 
   typedef float f32x4 __attribute__((ext_vector_type(4)));
