@@ -21,7 +21,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_case import Case, build
+from gpu_case import Case, build, launches
 from helpers import GRAD_TOL, f64, gather, grad_err
 from paper_2607_06827_amd import inputs
 from paper_2607_06827_amd import speechkv as skv
@@ -117,11 +117,12 @@ def check_attention_bwd(case):
         assert torch.isnan(dk[b, L:]).all() and torch.isnan(dv[b, L:]).all()
 
 
-# Sequences at the edges of the dK/dV blocks (16 and 64 keys) and of their
-# 16- and 32-row steps, from fewer steps than a block has waves or step groups
-# to some per group.  77 blocks of 14 steps or more take the bf16 kernel's groups
-# of two waves, the 616 blocks of 56 steps (8 KV heads) its three groups of four;
-# the short grids of CASES have one group.  (From two rows on: the
+# Sequences at the edges of the dK/dV blocks (16 keys in fp32, 32 and 64 in
+# bf16) and of their 16- and 32-row steps, from fewer steps than a block has waves
+# or step groups to some per group.  With one KV head (77 blocks of 64 keys, 14
+# steps or more) bf16 takes the groups of two waves and 32 keys, with eight (616
+# blocks, 56 steps) three groups of four waves and 64 keys; the short grids of
+# CASES have one group.  (From two rows on: the
 # dQ and dK of a single row are 0, which has no relative error.)
 EDGES = [2, 15, 16, 17, 31, 33, 63, 64, 65, 129, 417]
 
@@ -133,6 +134,38 @@ def test_attention_bwd_at_block_edges(dtype, D, Hq, Hkv):
     print(f"{dtype} D={D} Hq={Hq} Hkv={Hkv}", flush=True)
     check_attention_bwd(Case(P=[n // 3 for n in EDGES], T=[n - n // 3 for n in EDGES],
                              N=[0] * len(EDGES), layer=2, l0=5, D=D, Hq=Hq, Hkv=Hkv, dtype=dtype))
+
+
+# The bf16 dK/dV kernel's shapes, by threads a block, over pooled keys under the
+# window-start mask: groups of two waves (four groups at d = 128, eight at 64),
+# three groups of four, one group of four.
+def _mixed(B, P, T, N, **kw):
+    """B sequences from P + T + N rows downwards, the last one empty."""
+    cut = [(0 if b == 0 else 5 * b) for b in range(B - 1)]
+    return Case(P=[P - c // 2 for c in cut] + [0], T=[T - c for c in cut] + [0], N=[N - min(N, c // 8) for c in cut] + [0],
+                mode=1, **kw)
+
+
+DKDV_SHAPES = [
+    (512, _mixed(5, 90, 250, 9, D=128, Hq=8, Hkv=2)),
+    (1024, _mixed(5, 90, 250, 9, D=64, Hq=8, Hkv=2)),
+    (768, _mixed(9, 150, 260, 7, D=128, Hq=64, Hkv=16)),
+    (768, _mixed(9, 150, 260, 7, D=64, Hq=64, Hkv=16)),
+    (256, _mixed(10, 250, 60, 2, D=128, Hq=16, Hkv=16)),
+    (256, _mixed(10, 250, 60, 2, D=64, Hq=16, Hkv=16)),
+]
+
+
+@pytest.mark.parametrize("threads,case", DKDV_SHAPES, ids=lambda x: f"d{x.D}" if isinstance(x, Case) else str(x))
+def test_attention_bwd_block_shapes(threads, case):
+    print(f"{threads} threads: {case}", flush=True)
+    check_attention_bwd(case)
+    x = build(case)
+    out, lse = forward(case, x)
+    case_q, dout, cap = x["q"].to(x["dev"]), torch.zeros_like(out), max(x["clen"]) + 3
+    x["t"] = lambda q: case_q  # (nothing is copied during the capture)
+    run = launches(lambda: attention_bwd(case, x, out, lse, dout, cap))
+    assert run[-1][1] == threads, run
 
 
 POOL_CASES = {k: CASES[k] for k in ("bf16-d128", "bf16-d64-g1", "f32-d64", "identity-below-l0",

@@ -8,7 +8,7 @@ Sizes span several tiles and a ragged tail while the oracle stays fast.
 import pytest
 import torch
 
-from gpu_case import Case, build, run_and_check
+from gpu_case import Case, build, launches, run_and_check
 from paper_2607_06827_amd import speechkv as skv
 
 pytestmark = [pytest.mark.gpu,
@@ -78,6 +78,28 @@ F32_CASES = {
 def test_f32_prefill_kernels_match_oracle(name):
     print(f"case {name}", flush=True)
     run_and_check(F32_CASES[name])
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_f32_prefill_shared_tiles(D, G):
+    """The kernel of shared tiles, for every group and head size: two row tiles
+    for most sequences, an empty one, both masks, pages of 8 and 16, copied
+    (group 8) and pooled keys."""
+    Hkv, rows = 8, {1: 128, 2: 64, 4: 32, 8: 32}[G]
+    B = (513 if D == 64 else 257) // (2 * Hkv) + 2
+    n = rows + 19
+    case = Case(P=[b % 7 for b in range(B - 1)] + [0], T=[n - 12 - b % 5 for b in range(B - 1)] + [0],
+                N=[b % 6 for b in range(B - 1)] + [0], w=1 + G % 5, mode=G % 3 == 2, D=D, Hq=G * Hkv, Hkv=Hkv,
+                dtype="f32", page_size=8 if G == 4 else 16, l0=5 if G == 8 else 0, decode_steps=1)
+    run_and_check(case)
+    x = build(case)
+    q = x["q"].to(x["dev"])
+    out = torch.empty_like(q)
+    run = launches(lambda: skv.speechkv_prefill_attn(q, x["cache"], x["spans"], case.w, case.layer, case.l0, out,
+                                                     mask_mode=case.mode))
+    tiles = B * Hkv * -(-x["S"] // rows)
+    assert tiles > (512 if D == 64 else 256) and run == [(tiles, 512 if G == 8 else 256)], run
 
 
 @pytest.mark.parametrize("Hkv,D", [(1, 64), (1, 128), (520, 64), (260, 128)])

@@ -15,6 +15,7 @@ import torch
 
 import oracle
 from oracle import segments as seg
+from gpu_case import launches
 from helpers import GRAD_TOL, TOL, f64, fwd_err, gather, grad_err
 from paper_2607_06827_amd import inputs
 from paper_2607_06827_amd import speechkv as skv
@@ -288,6 +289,57 @@ def check_backward(segs, **kw):
         if R < x["S"]:
             assert torch.isnan(g["dkr"][b, R:]).all()
     assert grad_err(f64(g["du"]), pu) <= tol["du"]
+
+
+def _turns(B, a, t, n, step=4):
+    """B sequences of two turns each around text, shorter by `step` frames from
+    one to the next, and an empty one."""
+    return [[(a, t - step * b), (b % 3, a + b), (n, 0)] for b in range(B - 1)] + [[]]
+
+
+# the bf16 dK/dV kernel's shapes by threads a block (see test_gpu_bwd.py), with a
+# segment table: (threads, segments, arguments)
+DKDV_SHAPES = [
+    (512, _turns(5, 60, 200, 9), dict(D=128, Hq=8, Hkv=2, mode=1)),
+    (1024, _turns(5, 60, 200, 9), dict(D=64, Hq=8, Hkv=2, w=3)),
+    (768, _turns(9, 110, 180, 20), dict(D=128, Hq=64, Hkv=16, mode=1, w=2)),
+    (768, _turns(9, 110, 180, 20), dict(D=64, Hq=64, Hkv=16, w=2)),
+    (256, _turns(10, 100, 40, 130, step=2), dict(D=128, Hq=16, Hkv=16, w=5)),
+    (256, _turns(10, 100, 40, 130, step=2), dict(D=64, Hq=16, Hkv=16, mode=1, w=5)),
+]
+
+
+@pytest.mark.parametrize("threads,segs,kw", DKDV_SHAPES, ids=lambda x: str(x.get("D", "")) if isinstance(x, dict)
+                         else str(x) if isinstance(x, int) else "")
+def test_segments_backward_block_shapes(threads, segs, kw):
+    print(f"{threads} threads: {kw}", flush=True)
+    check_backward(segs, **kw)
+    x, clen, dout, g = run_backward(segs, **kw)
+    Hq, S = x["q"].shape[2], x["S"]
+    q, lse = x["q"].cuda(), torch.zeros(x["B"], Hq, S, device="cuda")
+    ws = torch.empty(skv.speechkv_prefill_attn_bwd_workspace_bytes(x["B"], Hq, S), dtype=torch.uint8, device="cuda")
+    run = launches(lambda: skv.speechkv_prefill_attn_bwd_segments(
+        q, x["cache"], x["segs"], kw.get("w", 4), 1, 0, dout, lse, dout, g["dq"], g["dkh"], g["dvh"], ws,
+        mask_mode=kw.get("mode", 0)))
+    assert run[-1][1] == threads, run
+
+
+# the fp32 forward of shared K/V tiles (more than 512 row tiles of 128 / G rows at
+# 64-wide heads, 256 at 128-wide), with a segment table
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_segments_f32_shared_tiles(D, G):
+    Hkv, rows = 8, {1: 128, 2: 64, 4: 32, 8: 32}[G]
+    B = (513 if D == 64 else 257) // (2 * Hkv) + 2
+    n = rows + 17  # two row tiles for most sequences
+    segs = [[(3 + b % 4, n // 3 + b % 5), (b % 3, n // 3), (n // 4, 0)] for b in range(B - 1)] + [[(2, 9)]]
+    kw = dict(w=1 + G % 5, mode=G % 3 == 2, D=D, Hq=G * Hkv, Hkv=Hkv, dtype="f32", page_size=8 if G == 4 else 16)
+    x, _, out, lse = check(segs, **kw)
+    q = x["q"].cuda()
+    run = launches(lambda: skv.speechkv_prefill_attn_segments(q, x["cache"], x["segs"], kw["w"], 1, 0, out,
+                                                              mask_mode=kw["mode"], lse=lse))
+    tiles = B * Hkv * -(-max(x["rows"]) // rows)
+    assert tiles > (512 if D == 64 else 256) and run == [(tiles, 512 if G == 8 else 256)], run
 
 
 def test_one_run_table_backward_equals_one_run_calls():
