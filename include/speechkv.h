@@ -464,6 +464,8 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
  *                row c of sequence b is the gradient of cache slot c.  Rows
  *                c >= min(P+nW+N, hat_capacity) are not written.  Caller
  *                obligation: hat_capacity >= P+nW+N for the full gradient.
+ *                The blocks are shaped for min(max_total_len, hat_capacity)
+ *                keys: the longest P+nW+N is the fastest capacity.
  * workspace      device, >= speechkv_prefill_attn_bwd_workspace_bytes bytes,
  *                16-byte aligned; receives Delta.
  * Nothing written may overlap an input or another output (ALIAS).

@@ -23,7 +23,7 @@
 //   stored output; the exact Delta accumulates beside it, and at the end
 //   dQ = scale (dZ0 K^ + (Delta0 - Delta) Kbar), Kbar = P K^.  It saves
 //   Delta for:
-// dK/dV kernel - a block owns a few keys (16 in fp32, 64 in bf16) of one
+// dK/dV kernel - a block owns a few keys (16 in fp32, 64 or 32 in bf16) of one
 //   (sequence, KV head) and walks the (query head, query tile) steps that see
 //   them; each step's Q / dO tile is staged in LDS by direct loads, K and V
 //   held in registers
@@ -33,7 +33,8 @@
 // The fp32 dK/dV kernel runs every product on the 16x16x4 fp32 MFMA (the fp32
 // dQ kernel is in prefill_f32.hip).  The bf16 kernels keep this split and these
 // formulas on the 16x16x32 bf16 MFMA with small per-wave tiles (16 query rows,
-// or 16 keys, a wave), so that three waves share each SIMD; P and dZ are
+// or 16 keys, a wave), so that three waves or more share each SIMD (two in the
+// dK/dV blocks of 32 keys at d = 128, whose buffers fill the LDS); P and dZ are
 // rounded to bf16 as MFMA operands, every product accumulates in fp32, and
 // dK^ and dV^ are written in fp32.
 // The mask's visibility rule comes from the span view (spans.hpp): one run
@@ -60,20 +61,19 @@ __device__ __forceinline__ float frag_dot(bf16x8_t x, bf16x8_t y) {
 
 // --------------------------------------------------------------- dK / dV
 
-// Q / dO tiles of the dK/dV kernel: 32 unpadded rows in LDS, filled by
+// bf16 tiles (Q and dO in dK/dV, K and V in dQ): 32 unpadded rows in LDS, filled by
 // direct loads (global_load_lds: a wave-wide load writes 64 x 16 bytes in
 // lane order), 16-byte chunks XOR-swizzled within a row: chunk c of row r sits
 // at position c ^ swz(r), so the operand reads of 16 rows at one chunk hit
 // distinct banks.
-template <typename T, int D>
+template <int D>
 struct QTile {
-  static constexpr int kElems16 = 16 / (int)sizeof(T);
-  static constexpr int kChunks = D / kElems16;              // 16-byte chunks per row
+  static constexpr int kChunks = D / 8;                     // 16-byte chunks per row
   static constexpr int kRowsPerLoad = 64 / kChunks;         // rows per wave-wide load
   static constexpr int kLoads = 32 / kRowsPerLoad;          // wave-wide loads per tile
   static constexpr int kElems = 32 * D;
   // XOR swizzle of the 16-byte chunks of row r.  With 16 chunks per row
-  // (bf16, D = 128: a row spans the 64 banks once) the tile is read both
+  // (D = 128: a row spans the 64 banks once) the tile is read both
   // transposed (ds_read_b64_tr_b16: 8 consecutive rows x 2 neighbouring
   // chunks per 32 lanes, so bits 1-3 differ over 8 consecutive rows) and
   // row-wise (16x16x32 A operands: lane group g reads rows 0-15 at chunk 4c +
@@ -85,11 +85,7 @@ struct QTile {
   // conflict: 2.0 conflict cycles per LDS instruction in dQ.)
   static __device__ __forceinline__ int swz(int r) {
     if constexpr (kChunks == 16) return (((r ^ ((r >> 1) & 4)) & 7) << 1) | ((r >> 3) & 1);
-    return r & (kChunks >= 16 ? 15 : kChunks - 1);
-  }
-  // element e of row r
-  static __device__ __forceinline__ int at(int r, int e) {
-    return r * D + (((e / kElems16) ^ swz(r)) * kElems16) + (e % kElems16);
+    return r & (kChunks - 1);
   }
 };
 
@@ -378,7 +374,7 @@ struct DqShape16 {
 template <int D, int G, bool kRuns>
 __global__ __launch_bounds__(DqShape16<G>::kThreads, 3) void prefill_bwd_dq16_kernel(PrefillBwdArgs a) {
   typedef bf16_bits T;
-  typedef QTile<T, D> Q;  // the K and V tiles: 32 rows, chunks swizzled per row
+  typedef QTile<D> Q;  // the K and V tiles: 32 rows, chunks swizzled per row
   typedef bf16x8_t Frag;
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   constexpr int kWaves = DqShape16<G>::kWaves;
@@ -673,7 +669,8 @@ __global__ __launch_bounds__(DqShape16<G>::kThreads, 3) void prefill_bwd_dq16_ke
 //
 // The bf16 dK/dV kernel on the 16x16x32 MFMA: a wave owns 16 keys, so its K
 // and V operands (16 VGPRs each at d = 128) and its dK^T and dV^T
-// accumulators (32 each) leave room for three waves per SIMD.  kWaves waves form
+// accumulators (32 each) leave room for three waves per SIMD (160 registers, no
+// scratch).  kWaves waves form
 // a step group with 16 kWaves keys of one (sequence, KV head), and the SG groups
 // of a block own the same keys and deal the (query head, 32-row query tile) steps
 // that see them round, so a block's chain of steps is 1 / SG of its keys'
@@ -697,7 +694,7 @@ __global__ __launch_bounds__(DqShape16<G>::kThreads, 3) void prefill_bwd_dq16_ke
 template <int D, bool kRuns, int kWaves, int SG, int kBufs>
 __global__ __launch_bounds__(64 * kWaves * SG, SG == 1 ? 3 : kWaves * SG / 4) void prefill_bwd_dkdv16_kernel(PrefillBwdArgs a) {
   typedef bf16_bits T;
-  typedef QTile<T, D> Q;
+  typedef QTile<D> Q;
   typedef bf16x8_t Frag;
   constexpr int kBlockKeys = 16 * kWaves;
   constexpr int kQ = 32;           // query rows per step
@@ -947,7 +944,8 @@ __global__ __launch_bounds__(64 * kWaves * SG, SG == 1 ? 3 : kWaves * SG / 4) vo
   };
 
   auto barrier_after = [&](int n) __attribute__((always_inline)) {
-    // step n+1's loads landed once only step n+2's are in flight
+    // step n+1's loads landed once only step n+2's are in flight (with two
+    // buffers, none)
     if (kBufs > 2 && n + 2 < n_steps) {
       if (my_vm == kVm) bare_barrier<kVm>();
       else bare_barrier<kVm + 1>();
@@ -1027,14 +1025,18 @@ hipError_t launch_dkdv(const PrefillBwdArgs& a, int batch, hipStream_t s) {
     // three blocks a CU all blocks of one step group are resident from the
     // start and the longest chain sets the time, so the steps are dealt out to
     // more groups: up to a block a CU to eight (d = 64) or four groups of two
-    // waves and 32 keys (us against three groups of four waves: 128 blocks of
-    // <= 196 steps 245 / 158, 144 of 180 109 / 72, 120 of 88 at d = 64 39.7 /
-    // 25.7, 224 of 100 63 / 46, 240 of 68 at d = 64 31.6 / 29.6, 20 of 16 18.4 /
-    // 13.9, 256 of 16 21.4 / 22.0, 448 of 98 76 / 89), up to three to three
-    // groups of four waves and 64 keys (one group / three: 512 of 100 107 / 84,
-    // 640 of 102 93 / 76).  The larger blocks pay their prologue and sums in
-    // the open, so more blocks, or short chains, keep one group (one / three:
-    // 2048 of 100 395 / 464, 560 of 24 46 / 54, 44 of 4 7.5 / 8.8).
+    // waves and 32 keys (us, one group of four waves / three / groups of two: 112
+    // blocks of <= 196 steps 160 / 102 / 71, 160 of 24 27 / 22 / 17, 160 of 92 at d
+    // = 64 61 / 37 / 23, 256 of 100 89 / 61 / 55, 256 of 18 22 / 21 / 25, 44 of 6
+    // 10.8 / 12.6 / 10.0), up to three to three groups of four waves and 64 keys
+    // (392 of 98 112 / 82 / 97, 512 of 100 106 / 90 / 109, 640 of 102 124 / 110 /
+    // 134).  The larger blocks pay their prologue and sums in the open, so more
+    // blocks, or short chains, keep one group (1024 of 100 195 / 175, where three
+    // would still pay, 2048 of 100 306 / 365, 448 of 24 31 / 36, 512 of 18 28 / 37).
+    // Both counts come from the caller's bounds: max_keys is the smaller of
+    // max_total_len and hat_capacity, so gradients allocated for more keys than
+    // the cache holds take the shape of that many (1596 x 471, b = 8, at a
+    // capacity of 1596: the backward 185 us, at 471 134).
     const int64_t chain = (int64_t)(a.num_q_heads / a.pv.kv_heads) * ((a.q_rows + 31) / 32);
     const int64_t blocks = (int64_t)batch * a.pv.kv_heads * ((a.max_keys + 63) / 64);
     if (blocks <= kCus && chain > 12)
