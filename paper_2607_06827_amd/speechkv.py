@@ -65,7 +65,8 @@ class _Segments(ctypes.Structure):
 # The descriptions above as packed bytes, passed by address: filling a cache
 # description takes 1.0 us instead of 1.7 with a ctypes structure, and a
 # decoding step of one sequence is bound by this path.  ctypes then takes any
-# of them for any other, so each _c below checks the type of its object.
+# of them for any other, so each kind is packed by a method of its own name
+# (see _Description).
 _pack_paged_kv = struct.Struct("@PPPiiiiii").pack
 _pack_spans = struct.Struct("@PPPii").pack
 _pack_segments = struct.Struct("@PPPiii4x").pack  # (padded to the structure's 8-byte alignment)
@@ -154,8 +155,18 @@ class SpeechKVError(RuntimeError):
         self.status = status
 
 
+class _Description:
+    """What the cache and span descriptions share: each has the packing that
+    the calls ask it for, and refuses the two that it is not."""
+
+    def _other_kind(self) -> bytes:
+        raise TypeError(f"{type(self).__name__} given where the call takes another description")
+
+    _paged_kv = _spans = _segments = _other_kind
+
+
 @dataclasses.dataclass
-class PagedKV:
+class PagedKV(_Description):
     """One layer's paged cache: k_pages/v_pages [num_pages, Hkv, page_size, D]
     and block_table [B, max_pages_per_seq] int32, all on the device."""
 
@@ -163,9 +174,7 @@ class PagedKV:
     v_pages: torch.Tensor
     block_table: torch.Tensor
 
-    def _c(self) -> bytes:
-        if not isinstance(self, PagedKV):
-            raise TypeError(f"expected a PagedKV, not {type(self).__name__}")
+    def _paged_kv(self) -> bytes:
         k, v, t = self.k_pages, self.v_pages, self.block_table
         if not (k.is_contiguous() and v.is_contiguous() and t.is_contiguous()):
             raise ValueError("paged cache tensors must be contiguous")
@@ -184,7 +193,7 @@ class PagedKV:
 
 
 @dataclasses.dataclass
-class Spans:
+class Spans(_Description):
     """Per-sequence text-prefix, speech and text-suffix lengths (device int32
     [B]) with host-side upper bounds."""
 
@@ -194,9 +203,7 @@ class Spans:
     max_speech_len: int
     max_total_len: int
 
-    def _c(self) -> bytes:
-        if not isinstance(self, Spans):
-            raise TypeError(f"expected Spans, not {type(self).__name__}")
+    def _spans(self) -> bytes:
         for x in (self.prefix_len, self.speech_len, self.suffix_len):
             if x.dtype != torch.int32 or not x.is_contiguous():
                 raise ValueError("span lengths must be contiguous int32 tensors")
@@ -208,7 +215,7 @@ class Spans:
 
 
 @dataclasses.dataclass
-class Segments:
+class Segments(_Description):
     """Sequences with several speech runs: sequence b is its segments
     [seg_start[b], seg_start[b+1]), segment i being text_len[i] text rows then
     speech_len[i] speech frames (device int32 tensors), with host-side bounds
@@ -220,9 +227,7 @@ class Segments:
     max_segments: int
     max_total_len: int
 
-    def _c(self) -> bytes:
-        if not isinstance(self, Segments):
-            raise TypeError(f"expected Segments, not {type(self).__name__}")
+    def _segments(self) -> bytes:
         for x in (self.seg_start, self.text_len, self.speech_len):
             if x.dtype != torch.int32 or not x.is_contiguous():
                 raise ValueError("segment tables must be contiguous int32 tensors")
@@ -282,8 +287,8 @@ def speechkv_pool_kv(k_raw: torch.Tensor, v_raw: torch.Tensor, spans: Spans, w: 
     if k_raw.dim() != 4 or k_raw.stride(3) != 1:
         raise ValueError("raw K/V must be [B, S, Hkv, D] with a contiguous last axis")
     sb, ss, sh, _ = k_raw.stride()
-    c = PagedKV._c(cache)
-    s = Spans._c(spans)
+    c = cache._paged_kv()
+    s = spans._spans()
     st = _lib.speechkv_pool_kv(k_raw.data_ptr(), v_raw.data_ptr(), sb, ss, sh, k_raw.shape[0],
                                k_raw.shape[1], s, w, _ptr(gate_u), layer, l0,
                                c, _ptr(cache_len_out), _stream(stream))
@@ -299,8 +304,8 @@ def speechkv_pool_kv_segments(k_raw: torch.Tensor, v_raw: torch.Tensor, segs: Se
     if k_raw.dim() != 4 or k_raw.stride(3) != 1:
         raise ValueError("raw K/V must be [B, S, Hkv, D] with a contiguous last axis")
     sb, ss, sh, _ = k_raw.stride()
-    c = PagedKV._c(cache)
-    g = Segments._c(segs)
+    c = cache._paged_kv()
+    g = segs._segments()
     st = _lib.speechkv_pool_kv_segments(k_raw.data_ptr(), v_raw.data_ptr(), sb, ss, sh,
                                         k_raw.shape[0], k_raw.shape[1], g, w,
                                         _ptr(gate_u), layer, l0, c,
@@ -319,8 +324,8 @@ def speechkv_prefill_attn_segments(q: torch.Tensor, cache: PagedKV, segs: Segmen
     B, q_len, Hq, D = q.shape
     if scale is None:
         scale = D ** -0.5
-    c = PagedKV._c(cache)
-    g = Segments._c(segs)
+    c = cache._paged_kv()
+    g = segs._segments()
     st = _lib.speechkv_prefill_attn_segments(q.data_ptr(), B, Hq, q_len, c,
                                              g, w, layer, l0, mask_mode, scale,
                                              out.data_ptr(), _ptr(lse), _stream(stream))
@@ -344,7 +349,7 @@ def speechkv_pool_hidden(h: torch.Tensor, spans: Spans, w: int, gate_u: Optional
         raise ValueError("h and out must be [B, S, hidden] with a contiguous last axis")
     if h.dtype != out.dtype or h.shape[0] != out.shape[0] or h.shape[2] != out.shape[2]:
         raise ValueError("h and out must agree in dtype, batch and hidden size")
-    s = Spans._c(spans)
+    s = spans._spans()
     st = _lib.speechkv_pool_hidden(h.data_ptr(), h.stride(0), h.stride(1), h.shape[0], h.shape[1],
                                    h.shape[2], _dtype_code(h.dtype), s, w,
                                    _ptr(gate_u), out.data_ptr(), out.stride(0), out.stride(1),
@@ -365,7 +370,7 @@ def speechkv_decode_attn(q: torch.Tensor, cache: PagedKV, cache_len: torch.Tenso
     B, Hq, D = q.shape
     if scale is None:
         scale = D ** -0.5
-    c = PagedKV._c(cache)
+    c = cache._paged_kv()
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = _lib.speechkv_decode_attn(q.data_ptr(), B, Hq, c, cache_len.data_ptr(),
                                    max_cache_len, _ptr(k_new), _ptr(v_new), scale, num_splits,
@@ -387,7 +392,7 @@ def speechkv_decode_attn_noalloc(q: torch.Tensor, cache: PagedKV, cache_len: tor
     B, Hq, D = q.shape
     if scale is None:
         scale = D ** -0.5
-    c = PagedKV._c(cache)
+    c = cache._paged_kv()
     st = _lib.speechkv_decode_attn_noalloc(q.data_ptr(), B, Hq, c,
                                            cache_len.data_ptr(), max_cache_len, _ptr(k_new),
                                            _ptr(v_new), scale, num_splits, out.data_ptr(),
@@ -406,8 +411,8 @@ def speechkv_prefill_attn(q: torch.Tensor, cache: PagedKV, spans: Spans, w: int,
     B, q_len, Hq, D = q.shape
     if scale is None:
         scale = D ** -0.5
-    c = PagedKV._c(cache)
-    s = Spans._c(spans)
+    c = cache._paged_kv()
+    s = spans._spans()
     st = _lib.speechkv_prefill_attn(q.data_ptr(), B, Hq, q_len, c, s,
                                     w, layer, l0, mask_mode, scale, out.data_ptr(), _ptr(lse),
                                     _stream(stream))
@@ -434,8 +439,8 @@ def speechkv_pool_prefill_attn(q: torch.Tensor, k_raw: torch.Tensor, v_raw: torc
     if scale is None:
         scale = D ** -0.5
     sb, ss, sh, _ = k_raw.stride()
-    c = PagedKV._c(cache)
-    s = Spans._c(spans)
+    c = cache._paged_kv()
+    s = spans._spans()
     st = _lib.speechkv_pool_prefill_attn(q.data_ptr(), B, Hq, q_len, k_raw.data_ptr(),
                                          v_raw.data_ptr(), sb, ss, sh, k_raw.shape[1],
                                          s, w, _ptr(gate_u), layer, l0,
@@ -456,7 +461,7 @@ def speechkv_prefill_attn_bwd(q: torch.Tensor, cache: PagedKV, spans: Spans, w: 
     """q, out, dout, dq: [B, q_len, Hq, D]; lse: [B, Hq, q_len] fp32;
     dk_hat, dv_hat: [B, hat_capacity, Hkv, D] fp32; workspace: device bytes."""
     _prefill_attn_bwd(_lib.speechkv_prefill_attn_bwd, "speechkv_prefill_attn_bwd", q, cache,
-                      Spans._c(spans), w, layer, l0, out, lse, dout, dq, dk_hat, dv_hat, workspace,
+                      spans._spans(), w, layer, l0, out, lse, dout, dq, dk_hat, dv_hat, workspace,
                       mask_mode, scale, stream)
 
 
@@ -468,7 +473,7 @@ def speechkv_prefill_attn_bwd_segments(q: torch.Tensor, cache: PagedKV, segs: Se
                                        scale: Optional[float] = None, stream=None) -> None:
     """speechkv_prefill_attn_bwd for sequences given as segment tables."""
     _prefill_attn_bwd(_lib.speechkv_prefill_attn_bwd_segments, "speechkv_prefill_attn_bwd_segments",
-                      q, cache, Segments._c(segs), w, layer, l0, out, lse, dout, dq, dk_hat, dv_hat,
+                      q, cache, segs._segments(), w, layer, l0, out, lse, dout, dq, dk_hat, dv_hat,
                       workspace, mask_mode, scale, stream)
 
 
@@ -484,7 +489,7 @@ def _prefill_attn_bwd(fn, name, q, cache, s, w, layer, l0, out, lse, dout, dq, d
     B, q_len, Hq, D = q.shape
     if scale is None:
         scale = D ** -0.5
-    c = PagedKV._c(cache)
+    c = cache._paged_kv()
     st = fn(q.data_ptr(), B, Hq, q_len, c, s, w, layer, l0, mask_mode,
             scale, out.data_ptr(), lse.data_ptr(), dout.data_ptr(), dq.data_ptr(),
             dk_hat.data_ptr(), dv_hat.data_ptr(), dk_hat.shape[1], workspace.data_ptr(),
@@ -506,7 +511,7 @@ def speechkv_pool_kv_bwd(k_raw: torch.Tensor, v_raw: torch.Tensor, spans: Spans,
     """k_raw, v_raw, dk_raw, dv_raw: [B, S_raw, Hkv, D] with one stride and a
     contiguous last axis; dk_hat, dv_hat: [B, capacity, Hkv, D] fp32; du:
     [Hkv, D] fp32 or None."""
-    _pool_kv_bwd(_lib.speechkv_pool_kv_bwd, "speechkv_pool_kv_bwd", k_raw, v_raw, Spans._c(spans), w,
+    _pool_kv_bwd(_lib.speechkv_pool_kv_bwd, "speechkv_pool_kv_bwd", k_raw, v_raw, spans._spans(), w,
                  gate_u, layer, l0, dk_hat, dv_hat, dk_raw, dv_raw, du, workspace, stream)
 
 
@@ -518,7 +523,7 @@ def speechkv_pool_kv_bwd_segments(k_raw: torch.Tensor, v_raw: torch.Tensor, segs
                                   workspace: Optional[torch.Tensor] = None, stream=None) -> None:
     """speechkv_pool_kv_bwd for sequences given as segment tables."""
     _pool_kv_bwd(_lib.speechkv_pool_kv_bwd_segments, "speechkv_pool_kv_bwd_segments", k_raw, v_raw,
-                 Segments._c(segs), w, gate_u, layer, l0, dk_hat, dv_hat, dk_raw, dv_raw, du, workspace,
+                 segs._segments(), w, gate_u, layer, l0, dk_hat, dv_hat, dk_raw, dv_raw, du, workspace,
                  stream)
 
 

@@ -669,12 +669,13 @@ def test_binding_refuses_spans_for_a_cache(call, given):
         binding_calls(d, d, d[given])[call]()
 
 
-@pytest.mark.parametrize("name,struct", [("cache", skv._PagedKV), ("spans", skv._Spans), ("segs", skv._Segments)])
-def test_packed_descriptions_fill_their_c_structures(name, struct):
+@pytest.mark.parametrize("name,pack,struct", [("cache", "_paged_kv", skv._PagedKV), ("spans", "_spans", skv._Spans),
+                                              ("segs", "_segments", skv._Segments)])
+def test_packed_descriptions_fill_their_c_structures(name, pack, struct):
     """The bytes the library is handed are as long as the structure it reads,
     and read back field by field as what the object holds."""
     x = descriptions()[name]
-    packed = x._c()
+    packed = getattr(x, pack)()
     assert len(packed) == ctypes.sizeof(struct)
     c = struct.from_buffer_copy(packed)
     if name == "cache":
