@@ -384,6 +384,8 @@ int speechkv_decode_attn_noalloc(const void* q, int32_t batch, int32_t num_q_hea
  * scale          logit scale, finite and > 0; 1/sqrt(head_dim) in the paper.
  * lse            device fp32 [batch][num_q_heads][q_len] receiving the
  *                natural-log log-sum-exp of each row's scaled logits, or NULL.
+ * The same call gives the same bits; in fp32 the order of a row's sums, and so
+ * its last bits, depends on the size of the batch it is in.
  * Errors: INVALID_ARG, UNSUPPORTED, HIP; ALIAS when out or lse overlaps q, a
  *         page pool, the block table, the span lengths or each other.
  */
@@ -468,6 +470,8 @@ int speechkv_pool_prefill_attn(const void* q, int32_t batch, int32_t num_q_heads
  *                keys: the longest P+nW+N is the fastest capacity.
  * workspace      device, >= speechkv_prefill_attn_bwd_workspace_bytes bytes,
  *                16-byte aligned; receives Delta.
+ * The same call gives the same bits; in bf16 the order of the sums in dk_hat
+ * and dv_hat, and so their last bits, depends on the size of the batch.
  * Nothing written may overlap an input or another output (ALIAS).
  * Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE, ALIAS, HIP.
  */
