@@ -678,10 +678,10 @@ __global__ __launch_bounds__(DqShape16<G>::kThreads, 3) void prefill_bwd_dq16_ke
 // Each step's Q, dO, LSE and Delta are staged once in LDS for its group by
 // untracked direct loads, kBufs - 1 steps ahead, as in the forward, and each
 // wave reads its MFMA operands four ahead of the products.
-// (Read eight ahead at two waves per SIMD and SG = 2: 91 us at 1596 x 471, b =
-// 8, against 89 with SG = 3; 32 keys a wave on the 32x32x16 MFMA, which halves
-// the LDS reads, spills at two waves per SIMD: 105 us.)  Per step a wave
-// computes
+// (1596 x 471, b = 8: 77.6 us; 107 with one group.  Timed when SG = 3 took 89, with
+// bank conflicts and scratch: read eight ahead at two waves per SIMD and SG = 2
+// 91 us; 32 keys a wave on the 32x32x16 MFMA, which halves the LDS reads, spills
+// at two waves per SIMD, 105 us.)  Per step a wave computes
 //   S  = Q K^T  - LSE/scale    (two 16 x 16 blocks: query rows 0-15, 16-31)
 //   dP = dO V^T - Delta
 //   P = exp2(scale log2e S),  dZ = P dP     (masked)
