@@ -3,7 +3,8 @@
 // inside the forward pass).  One launch reads the raw K/V, pools every key
 // tile it needs in registers (the same steps as the pooling kernel, so the
 // same bits), attends over it under the causal mask over compressed positions
-// and writes each pooled row to the paged cache once.
+// and writes each pooled row to the paged cache once.  It takes the short calls,
+// where it saves a launch; the rule and both sides' times are in api.hip.
 #pragma once
 
 #include "kernels.hpp"
