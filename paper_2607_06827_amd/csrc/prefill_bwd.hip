@@ -300,6 +300,12 @@ __global__ __launch_bounds__(KvBwdShapeF32<D>::kThreads, KvBwdShapeF32<D>::kWave
   // them is all it waits for (the first wait covers the K/V loads too)
   Buf& b0 = s_buf[wave][0];
   Buf& b1 = s_buf[wave][1];
+  // The steps of the last query tile, where it is ragged: there the dO rows past
+  // the end, copies of the last one, are cleared (an infinite one would meet its
+  // zero weights in dV as 0 * infinity).  Out of line, the check costs 0% at d =
+  // 64 and 1% at d = 128; as a first step before the loop, whose code short
+  // chains fetch once more, up to 8%.
+  const int clear_steps = rows % kQ ? group : 0;
   auto step = [&](int n, Buf& cur, Buf& nxt) __attribute__((always_inline)) {
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(63));  // the last step's LDS reads are done before nxt is refilled
@@ -311,6 +317,10 @@ __global__ __launch_bounds__(KvBwdShapeF32<D>::kThreads, KvBwdShapeF32<D>::kWave
       __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
     }
     asm volatile("" ::: "memory");
+    if (__builtin_expect(n < clear_steps, false)) {
+      for (int i = (rows - (t1 - 1) * kQ) * kChunks + lane; i < kQ * kChunks; i += 64)
+        *reinterpret_cast<f32x4*>(cur.g + 4 * i) = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     __builtin_amdgcn_sched_barrier(0);
     compute(n, cur);
   };

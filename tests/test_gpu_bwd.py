@@ -341,3 +341,18 @@ def test_training_backward_at_benched_shape():
     eu = grad_err(f64(tj.du), ru)
     print(f"  pooling backward, whole batch: dk {ek:.2e} dv {ev:.2e} du {eu:.2e}", flush=True)
     assert ek <= tol["dkv_raw"] and ev <= tol["dkv_raw"] and eu <= tol["du"]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_infinite_gradient_stays_infinite_in_dv(D):
+    """The last row sees every key, so an infinite gradient there makes dV^
+    infinite, not NaN: the unused rows of the last tile must not meet their zero
+    weights as 0 * infinity."""
+    case = Case(P=[21], T=[0], N=[0], D=D, Hq=2, Hkv=1, dtype="f32")
+    x = build(case)
+    out, lse = forward(case, x)
+    dout = inputs.normal((1, x["S"], 2, D), 21, dtype=x["dt"]).to(x["dev"])
+    dout[:, -1] = float("inf")
+    _, _, dv = attention_bwd(case, x, out, lse, dout, 21)
+    torch.cuda.synchronize()
+    assert torch.isposinf(dv).all()
